@@ -142,7 +142,7 @@ marlin_status_t marlin_unpack_weights(const void *w_packed, const void *s_packed
  *              may overlap (different streams) need separate workspaces.
  *
  * Accumulation is fp32.  Group scales multiply each 128-row fp32 partial
- * product (stream kernel with row groups of up to 32 rows, tile kernel) or,
+ * product (stream kernel with row groups of up to 32 rows, tile kernels) or,
  * in the wide kernel that serves large batches and the stream and pair
  * kernels with 64-row groups, the fp16 weights before the product (one fp16 rounding per
  * weight, as Section 3.4's "Groups and Instruction Ordering" does);
@@ -156,9 +156,10 @@ marlin_status_t marlin_unpack_weights(const void *w_packed, const void *s_packed
  *
  * The launch configuration comes from a cost model of the device (see
  * marlin_describe).  For tuning and tests, the environment variable
- * MARLIN_FORCE_CONFIG="kind=<stream|tile|wide>,nb=<1|2|4|8>,whole=<0|1>,
+ * MARLIN_FORCE_CONFIG="kind=<stream|tile|tile8|wide>,nb=<1|2|4|8>,whole=<0|1|2>,
  * grid=<n>,waves=<4|8>,nw=<4|8>,ks=<1|2|4>,mb=<1|2|4>" (any subset: kernel,
- * column blocks per tile (per wave for the tile and wide kernels), partition,
+ * column blocks per tile (per wave for the tile and wide kernels), partition
+ * (2: the eight-wave kernels' hybrid of whole and shared tiles),
  * work-groups, stream-kernel waves per work-group (eight with mb=4: the
  * pair kernel), tile-kernel waves and 128-row blocks per stage,
  * stream-kernel 16-row blocks per row group)
@@ -216,8 +217,9 @@ marlin_status_t marlin_gemm_no_alloc(const uint16_t *A, const void *w_packed, co
  * <16-row blocks, 16-column blocks, ring depth, activation rows / 4, waves,
  * per-channel>, the tile kernel's <waves along N, waves along M, 16-row
  * blocks per wave, 16-column blocks per wave, 128-row blocks per stage,
- * per-channel>, the wide kernel's <16-row blocks per wave, 16-column blocks
- * per wave, ring depth, per-channel>.  Row groups are of 32 rows for the
+ * per-channel> (EightWaves<per-channel> for the one whose every operand goes
+ * through LDS), the wide kernel's <16-row blocks per wave, 16-column blocks
+ * per wave, ring depth, EightWaves<per-channel>>.  Row groups are of 32 rows for the
  * stream kernel and of the tile's rows for the tile and wide kernels.  Pure
  * host code apart from
  * reading the device's compute-unit count; enqueues nothing.

@@ -19,7 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libmarlin_mi355x.so")
-SOURCES = ["api.cpp", "plan.cpp", "gemm.hip", "pair.hip", "tile.hip", "wide.hip", "pack.hip", "quant.hip", "noalloc.hip"]
+SOURCES = ["api.cpp", "plan.cpp", "gemm.hip", "pair.hip", "tile.hip", "tile8.hip", "wide.hip", "pack.hip", "quant.hip", "noalloc.hip"]
 ARCH = "gfx950"
 
 # Packed fp32 instructions are disabled for all device code: plain float code
@@ -29,9 +29,7 @@ ARCH = "gfx950"
 # stage reads them without accumulator-register moves.
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                 "-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-# The wide kernel's accumulators are written by MFMAs only, so it lets the
-# compiler place them in the accumulation registers.
-SOURCE_FLAGS = {"wide.hip": ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]}
+SOURCE_FLAGS: dict[str, list[str]] = {}  # sources with flags of their own
 _NOISE = "is not a recognized feature for this target"
 
 

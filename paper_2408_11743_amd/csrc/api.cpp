@@ -116,7 +116,8 @@ marlin_status_t marlin::gemm_entry(const uint16_t *A, const void *w_packed, cons
         p.G = (int)G;
         p.KU = (int)(K / 128);
         p.rg = cfg.rg;
-        p.units = (int)(N / tile_cols(cfg)) * cfg.rg * p.KU;
+        p.tiles = (int)((N + tile_cols(cfg) - 1) / tile_cols(cfg)) * cfg.rg;
+        p.units = (cfg.hybrid ? p.tiles % cfg.grid : p.tiles) * p.KU;
         p.gran = cfg.whole ? p.KU : 1;
         p.per_wg = (p.units / p.gran) / cfg.grid;
         p.extra = (p.units / p.gran) % cfg.grid;

@@ -318,5 +318,74 @@ __device__ __forceinline__ void combine_tiles(const GemmProblem &p, int *flags, 
     if (reduce_first) reduce(c_first, false);
 }
 
+// ---- 16-byte partial slots, combined wave by wave ----
+// The kernels with large tiles (16 blocks per wave, 64 or 128 KiB per slot)
+// keep a block as 64 float4, lane by lane (block at float4 index blk*64), and
+// move it with 16-byte accesses that carry the device-coherence bit (sc1), as
+// the dword accesses above do: a quarter of the instructions and four times
+// the bytes in flight.
+constexpr int kAuxDeviceCoherent = 16;  // cache-policy bit sc1
+
+__device__ __forceinline__ void store_partial16(float *slot, int blk, int lane, float4_t v)
+{
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc((void *)slot, (short)0, 0x7fffffffu, kBufferFlags);
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), r, lane * 16, blk * 1024, kAuxDeviceCoherent);
+}
+
+__device__ __forceinline__ float4_t load_partial16(const float *slot, int blk, int lane)
+{
+    const __amdgpu_buffer_rsrc_t r =
+        __builtin_amdgcn_make_buffer_rsrc((void *)slot, (short)0, 0x7fffffffu, kBufferFlags);
+    return __builtin_bit_cast(float4_t, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16, blk * 1024, kAuxDeviceCoherent));
+}
+
+// Shared tiles of those kernels are combined wave by wave: wave w of every
+// contributor arrives at word w of the tile's counter line once its stores are
+// complete, and whichever arrives last sums the contributors' blocks in
+// work-group order and writes C.  No wave waits for another, there is no
+// barrier, and the reduction of a tile is spread over the work-groups whose
+// waves happen to be last.
+
+// This wave's arrival at tile c: true for the last one (its counter is reset).
+__device__ __forceinline__ bool arrive_by_wave(const GemmProblem &p, int c, int wave, int grid, int lane)
+{
+    const int wf = unit_owner(p, c * p.KU, grid), wl = unit_owner(p, c * p.KU + p.KU - 1, grid);
+    uint32_t *const ctr = p.counters + kCounterStride * wf + wave;
+    uint32_t seen = 0;
+    if (lane == 0) {
+        seen = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (seen == (uint32_t)(wl - wf)) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const bool last = __builtin_amdgcn_readfirstlane((int)seen) == wl - wf;
+    asm volatile("" ::: "memory");
+    return last;
+}
+
+// Tile c's blocks of this wave from the contributors' slots (own(j): slot block
+// of block j), work-group `skip`'s from `mine` (its registers; -1: none).
+template <int KOWN, typename OwnFn>
+__device__ __forceinline__ void reduce_by_wave(const GemmProblem &p, int c, int grid, int slot_floats, int lane,
+                                               OwnFn own, int skip, const float4_t (&mine)[KOWN],
+                                               float4_t (&out)[KOWN])
+{
+    const int wf = unit_owner(p, c * p.KU, grid);
+    const int wl = unit_owner(p, c * p.KU + p.KU - 1, grid);
+    for (int w = wf; w <= wl; ++w) {
+        const int w_last = tile_of(p, range_start(p, w + 1, grid) - 1);
+        const float *slot = p.partials + ((int64_t)w * 2 + (c == w_last ? 1 : 0)) * slot_floats;
+        float4_t v[KOWN];
+        if (w == skip) {
+#pragma unroll
+            for (int j = 0; j < KOWN; ++j) v[j] = mine[j];
+        } else {
+#pragma unroll
+            for (int j = 0; j < KOWN; ++j) v[j] = load_partial16(slot, own(j), lane);
+        }
+#pragma unroll
+        for (int j = 0; j < KOWN; ++j) out[j] = w == wf ? v[j] : out[j] + v[j];
+    }
+}
+
 }  // namespace dev
 }  // namespace marlin

@@ -843,12 +843,16 @@ hipError_t launch_stream(const GemmConfig &cfg, const GemmProblem &p, hipStream_
 
 void kernel_name(const GemmConfig &cfg, bool per_channel, char *buf, size_t n)
 {
+    if (cfg.kind == kKindTile8) {
+        tile8_kernel_name(cfg, per_channel, buf, n);
+        return;
+    }
     if (cfg.kind == kKindTile) {
         tile_kernel_name(cfg, per_channel, buf, n);
         return;
     }
     if (cfg.kind == kKindWide) {
-        wide_kernel_name(cfg, per_channel, buf, n);
+        wide_kernel_name(per_channel, buf, n);
         return;
     }
     if (cfg.mb == 4 && cfg.waves == 8) {
@@ -899,6 +903,7 @@ void kernel_name(const GemmConfig &cfg, bool per_channel, char *buf, size_t n)
 
 hipError_t launch_gemm(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream)
 {
+    if (cfg.kind == kKindTile8) return launch_tile8_gemm(cfg, p, stream);
     if (cfg.kind == kKindTile) return launch_tile_gemm(cfg, p, stream);
     if (cfg.kind == kKindWide) return launch_wide_gemm(cfg, p, stream);
     if (cfg.mb == 4 && cfg.waves == 8) return launch_pair_gemm(cfg, p, stream);

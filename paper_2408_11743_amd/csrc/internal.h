@@ -24,7 +24,8 @@ struct GemmProblem {
     int K;
     int G;                // scale rows
     int KU;               // 128-row blocks of K
-    int units;            // column tiles * KU: 128-row blocks of all column tiles
+    int units;            // column tiles * KU: 128-row blocks of all (with tiles beyond them: the shared) column tiles
+    int tiles;            // eight-wave tile and wide kernels: all tiles; those past units / KU are whole
     int gran;             // units per partition item: KU (whole tiles) or 1
     int per_wg;           // (units / gran) / grid
     int extra;            // (units / gran) % grid
@@ -58,7 +59,10 @@ void kernel_name(const GemmConfig &cfg, bool per_channel, char *buf, size_t n);
 hipError_t launch_tile_gemm(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream);
 void tile_kernel_name(const GemmConfig &cfg, bool per_channel, char *buf, size_t n);
 hipError_t launch_wide_gemm(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream);
-void wide_kernel_name(const GemmConfig &cfg, bool per_channel, char *buf, size_t n);
+void wide_kernel_name(bool per_channel, char *buf, size_t n);
+// The tile kernel with eight waves (tile8.hip).
+hipError_t launch_tile8_gemm(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream);
+void tile8_kernel_name(const GemmConfig &cfg, bool per_channel, char *buf, size_t n);
 // The stream kernel's 64-row tiles with eight waves (pair.hip).
 hipError_t launch_pair_gemm(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream);
 void pair_kernel_name(bool per_channel, char *buf, size_t n);

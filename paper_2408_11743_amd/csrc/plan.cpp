@@ -23,9 +23,10 @@ Override parse_override(const char *e)
     q = strstr(e, "grid=");
     if (q) f.grid = atoi(q + 5);
     q = strstr(e, "whole=");
-    if (q) f.whole = atoi(q + 6) ? 1 : 0;
+    if (q) f.whole = atoi(q + 6) == 2 ? 2 : atoi(q + 6) ? 1 : 0;
     if (strstr(e, "kind=stream")) f.kind = kKindStream;
     if (strstr(e, "kind=tile")) f.kind = kKindTile;
+    if (strstr(e, "kind=tile8")) f.kind = kKindTile8;
     if (strstr(e, "kind=wide")) f.kind = kKindWide;
     q = strstr(e, "ks=");
     if (q) f.ks = atoi(q + 3);
@@ -59,7 +60,7 @@ Override current_override()
 
 int slot_floats(const GemmConfig &cfg)
 {
-    if (cfg.kind == kKindTile) return cfg.tile_nw * cfg.nb * cfg.mb * 256;
+    if (cfg.kind == kKindTile || cfg.kind == kKindTile8) return cfg.tile_nw * cfg.nb * cfg.mb * 256;
     if (cfg.kind == kKindWide) return 4 * cfg.nb * cfg.mb * 256;
     return cfg.nb * cfg.mb * 256;
 }
@@ -206,13 +207,74 @@ Partition best_partition(const Override &ov, int64_t tiles, int KU, int64_t grid
     }
     return best;
 }
+// Eight-wave tile and wide kernels (256-column tiles): the time of a launch is the fixed
+// cost, plus per 128-row block of the busiest work-group's tiles a unit time
+// that grows with the share of the compute units in use (power and shared
+// bandwidth), plus what the partition adds: per tile of a work-group beyond its
+// first (epilogue), per split (combination, and per contributor) or for the
+// hybrid's shared tiles.  Fitted to 1189 timings on 13 layer shapes, 33 to 3000
+// rows (4-5% rms).
+struct TileFit {
+    double fixed_us, unit_us, unit_busy_us, tile_us, split_us, contributor_us, hybrid_us;
+};
+constexpr TileFit kWideFit = {10.4, 1.06, 0.54, 6.5, 1.9, 0.82, 14.5};     // wide, 128 x 256
+constexpr TileFit kTile128Fit = {8.4, 1.33, 0.49, 4.7, 1.9, 0.80, 12.5};  // tile, 128 x 256
+constexpr TileFit kTile64Fit = {6.2, 0.79, 0.26, 2.0, 1.8, 0.57, 8.9};    // tile, 64 x 256
+
+struct TilePartition {
+    double t;
+    int whole, hybrid;
+    int64_t grid;
+};
+
+// Whole tiles; each tile split evenly over up to 16 work-groups (the ranges'
+// ends then fall on tile boundaries, so every work-group has one segment and
+// writes one partial tile: measured 68 against 75 us for unaligned Stream-K
+// ranges on 8192 x 28672 at M = 128); or, with more tiles than work-groups,
+// the hybrid: a multiple of the work-groups whole, the rest shared by all of
+// them, first, so that their combination is not what every work-group ends on
+// (8192 x 10240 at M = 1024: 159 us, against 173 for Stream-K and 194 whole).
+TilePartition best_tile_partition(const Override &ov, int64_t tiles, int KU, int64_t grid, const TileFit &f,
+                                  size_t slot_bytes, size_t budget)
+{
+    TilePartition best{1e30, 1, 0, 1};
+    auto take = [&](double t, int whole, int hybrid, int64_t g) {
+        if (!whole && budget != SIZE_MAX && kCounterRegionBytes + (size_t)g * slot_bytes > budget) return;
+        if (t < best.t) best = {t, whole, hybrid, g};
+    };
+    const int64_t rounds = tiles / grid, rem = tiles % grid;
+    const double busy = f.unit_us + f.unit_busy_us;  // unit time with every compute unit in use
+    auto unit = [&](int64_t active) { return f.unit_us + f.unit_busy_us * (double)active / (double)kMaxCus; };
+    const bool hybrid = rounds > 0 && rem != 0;
+    if (ov.whole < 0 || ov.whole == 1 || (ov.whole == 2 && !hybrid)) {
+        const int64_t n = rounds + (rem != 0);
+        take(f.fixed_us + (double)KU * ((double)rounds * busy + (rem ? unit(rem) : 0.0)) + (double)(n - 1) * f.tile_us,
+             1, 0, tiles < grid ? tiles : grid);
+    }
+    if ((ov.whole < 0 || ov.whole == 2) && hybrid)
+        take(f.fixed_us + ((double)rounds * KU + (double)rem * KU / (double)grid) * busy +
+                 (double)rounds * f.tile_us + f.hybrid_us,
+             0, 1, grid);
+    if (ov.whole <= 0) {
+        if (ov.grid || (ov.whole == 0 && 2 * tiles > grid)) {  // forced: plain Stream-K ranges
+            const int64_t g = grid < tiles * KU ? grid : tiles * KU;
+            take(f.fixed_us + (double)tiles * KU / (double)g * unit(g) + f.hybrid_us, 0, 0, g);
+        } else {
+            for (int64_t s = 2; s <= KU && s <= 16 && tiles * s <= grid; ++s)
+                take(f.fixed_us + (double)((KU + s - 1) / s) * unit(tiles * s) + f.split_us +
+                         (double)s * f.contributor_us,
+                     0, 0, tiles * s);
+        }
+    }
+    return best;
+}
 }  // namespace
 
 GemmConfig choose_config(int M, int N, int K, int group_units, int cus, bool sparse, const Override &ov,
                          size_t partial_budget)
 {
-    (void)group_units;
     GemmConfig cfg;
+    cfg.hybrid = 0;
     const int KU = K / 128;
     const int tiles16 = N / 16;
     const int ncu = cus < kMaxCus ? cus : kMaxCus;
@@ -240,7 +302,7 @@ GemmConfig choose_config(int M, int N, int K, int group_units, int cus, bool spa
     cfg.whole = 0;
     int64_t best_grid = grid;
     for (int mb : {mb_small, 4}) {
-        if (ov.kind == kKindTile || ov.kind == kKindWide) break;
+        if (ov.kind > kKindStream) break;
         if (mb == 4 && !mb4_ok) continue;
         if (ov.mb && mb != ov.mb && (ov.mb == 4 ? mb4_ok : ov.mb == mb_small)) continue;
         const int ar = mb == 4 ? 16 : cfg.ar;
@@ -297,7 +359,7 @@ GemmConfig choose_config(int M, int N, int K, int group_units, int cus, bool spa
     // 128-row block per stage; up to 32 rows, 4x1 waves of 16 or 32 rows over
     // 2 or 4 blocks per stage (measured to win only where whole 128-column
     // tiles fill the chip at 17..32 rows, e.g. N = 28672).
-    if (!sparse && ov.kind != kKindStream && ov.kind != kKindWide) {
+    if (!sparse && ov.kind != kKindStream && ov.kind != kKindWide && ov.kind != kKindTile8) {
         for (int nw = 8; nw >= 4; nw -= 4) {
             if (ov.nw && nw != ov.nw) continue;
             // rows per tile: 64*wm with 64-row waves; eight waves at 33..64
@@ -334,36 +396,59 @@ GemmConfig choose_config(int M, int N, int K, int group_units, int cus, bool spa
             }
         }
     }
-    // wide kernel: four waves along N, each 64 x 128 or 128 x 64 outputs,
-    // weights in registers, activations and group scales shared in LDS.  One
-    // wave per SIMD: its dequantization and its MFMAs do not overlap, so it
-    // wins only where each dequantized weight feeds 128 rows, beyond 128 rows
-    // (measured per 128-row block of a tile: 1.92 us for 128 x 256 tiles,
-    // 2.15 us for 64 x 512; the combination reads 128 KiB fp32 slots).
-    if (!sparse && ov.kind != kKindStream && ov.kind != kKindTile && (M > 128 || ov.kind == kKindWide)) {
-        const int shapes[2][2] = {{8, 4}, {4, 8}};  // 16-row blocks, 16-column blocks per wave
-        for (const auto &sh : shapes) {
-            const int mbw = sh[0], nbw = sh[1];
-            if (ov.nb && nbw != ov.nb) continue;
-            const int cols = 64 * nbw, rows = 16 * mbw;
-            if (N % cols != 0) continue;
-            const int64_t tiles = (int64_t)(N / cols) * ((M + rows - 1) / rows);
-            const size_t slot_bytes = (size_t)2 * 4 * nbw * mbw * 256 * sizeof(float);
-            const double unit_us = mbw == 8 ? 1.92 : 2.15;
-            const Partition pt =
-                best_partition(ov, tiles, KU, grid, unit_us, 8.0, 2.0, 0.0, slot_bytes, partial_budget);
+    // Eight-wave tile and wide kernels (256-column tiles, the last one of any
+    // width).  The tile kernel scales each 128-row fp32 product, as the stream
+    // kernel does, and is weighed against all of the above.  The wide kernel
+    // rounds the scaled weights to fp16 (half of the tile kernel's conversion
+    // and scaling per MFMA, 10-15% faster beyond 256 rows), so with group
+    // scales it only takes calls that already go to row groups of 64, which do
+    // the same, or beyond 128 rows those for which a kernel with that rounding
+    // is at hand at 1.92 us per 128-row block of a 128 x 256 tile or 2.15 us
+    // of a 64 x 512 one (the four-wave kernels that served them): the others
+    // keep their fp32 scales.
+    // Up to 64 rows the row groups of 32 and 64 lead or are within 10%.  The
+    // times above are up to 15% too long for whole tiles (the row groups of one
+    // column tile share its weights in L2: 8192 x 8192 at M = 128 takes 25.2 us,
+    // modelled 28.4, where these kernels take 27.3) and 5-50% too short for
+    // Stream-K ranges over several row groups (23680 x 3200 at M = 280: 102 us,
+    // modelled 70.5), hence the two weights on the comparison.
+    if (!sparse && (ov.kind < 0 ? M > 64 : ov.kind == kKindWide || ov.kind == kKindTile8)) {
+        bool rounds_weights = group_units == 0 || (cfg.kind == kKindStream && cfg.mb == 4);
+        if (M > 128 && !rounds_weights) {
+            const int shapes[2][2] = {{128, 256}, {64, 512}};
+            for (const auto &sh : shapes) {
+                if (N % sh[1] != 0) continue;
+                const Partition pt = best_partition(ov, (int64_t)(N / sh[1]) * ((M + sh[0] - 1) / sh[0]), KU, grid,
+                                                    sh[0] == 128 ? 1.92 : 2.15, 8.0, 2.0, 0.0, (size_t)2 << 17,
+                                                    partial_budget);
+                rounds_weights = rounds_weights || pt.t < best;
+            }
+        }
+        if (ov.kind < 0) best *= cfg.whole ? 0.93 : 1.08;
+        for (int shape = 0; shape < 3; ++shape) {  // wide 128 x 256, tile 128 x 256, tile 64 x 256
+            const int kind = shape == 0 ? kKindWide : kKindTile8;
+            if (ov.kind >= 0 ? kind != ov.kind : (shape == 0 && !rounds_weights)) continue;
+            const int nb = shape == 2 ? 2 : 4;
+            if (kind == kKindTile8 && ov.nb && nb != ov.nb) continue;
+            const int rows = shape == 2 ? 64 : 128;
+            const int64_t tiles = (int64_t)((N + 255) / 256) * ((M + rows - 1) / rows);
+            const size_t slot_bytes = (size_t)2 * 8 * (shape == 2 ? 8 : 16) * 256 * sizeof(float);
+            const TilePartition pt =
+                best_tile_partition(ov, tiles, KU, grid, shape == 0 ? kWideFit : shape == 1 ? kTile128Fit : kTile64Fit,
+                                    slot_bytes, partial_budget);
             if (pt.t < best) {
                 best = pt.t;
-                cfg.kind = kKindWide;
-                cfg.tile_nw = 4;
-                cfg.tile_wm = 1;
+                cfg.kind = kind;
+                cfg.tile_nw = 8;
+                cfg.tile_wm = shape == 1 ? 2 : 1;
                 cfg.tile_ks = 1;
                 cfg.waves = 0;
-                cfg.nb = nbw;
-                cfg.mb = mbw;
+                cfg.nb = nb;
+                cfg.mb = shape == 0 ? 8 : 4;
                 cfg.ar = 0;
                 cfg.rg = (M + rows - 1) / rows;
                 cfg.whole = pt.whole;
+                cfg.hybrid = pt.hybrid;
                 best_grid = pt.grid;
             }
         }

@@ -14,6 +14,7 @@ constexpr int kStreamOcc = 1;  // stream kernel work-groups per compute unit
 
 constexpr int kKindStream = 0;  // w4a16_stream_kernel (any M; row groups of 32)
 constexpr int kKindTile = 1;    // w4a16_tile_kernel (activation tile shared by the waves)
+constexpr int kKindTile8 = 3;   // w4a16_tile_kernel of tile8.hip (every operand through LDS, two waves per SIMD)
 constexpr int kKindWide = 2;    // w4a16_wide_kernel (four waves along N, weights in registers)
 
 // One launch configuration of the GEMM kernel.
@@ -42,14 +43,16 @@ struct GemmConfig {
     int tile_ks;  // tile kernel: 128-row blocks of K per work-group stage
     int tile_nw;  // tile kernel: waves per work-group (4 or 8)
     int waves;    // stream kernel: waves per work-group (4 or 8)
+    int hybrid;   // eight-wave tile and wide kernels: the tiles beyond a multiple of grid are
+                  // shared by all work-groups (Stream-K ranges, done first), the others whole
 };
 
 // Columns and rows of one tile of a configuration.
 inline int tile_cols(const GemmConfig &c)
 {
-    return c.kind == kKindTile ? (c.tile_nw / c.tile_wm) * 16 * c.nb : c.kind == kKindWide ? 64 * c.nb : 16 * c.nb;
+    return c.kind == kKindTile || c.kind == kKindTile8 ? (c.tile_nw / c.tile_wm) * 16 * c.nb : c.kind == kKindWide ? 64 * c.nb : 16 * c.nb;
 }
-inline int tile_rows(const GemmConfig &c) { return c.kind == kKindTile ? c.tile_wm * 16 * c.mb : 16 * c.mb; }
+inline int tile_rows(const GemmConfig &c) { return c.kind == kKindTile || c.kind == kKindTile8 ? c.tile_wm * 16 * c.mb : 16 * c.mb; }
 
 // ceil(2^32 / d) for 2 <= d: with it, floor(n / d) = floor(n * m / 2^32) for
 // every n with n * d <= 2^32 (m = (2^32 + e) / d, 0 <= e < d, so the error

@@ -1,30 +1,33 @@
-// W4A16 GEMM for gfx950 at batches of 33 rows and more, where every
-// dequantized weight must feed many rows of A:
-// C[M,N] = A[M,K] * (s * (q - 8)), fp32 accumulation.
+// W4A16 GEMM for gfx950 at prefill batches: C[M,N] = A[M,K] * (s * (q - 8)),
+// fp32 accumulation, group scales on the fp16 weights.
 //
-//  * A work-group of four waves (one per SIMD) owns a tile of 16*MBW rows x
-//    4*16*NBW columns; each wave owns 16*MBW rows x 16*NBW columns, 32
-//    16x16 accumulator blocks (MBW * NBW = 32).  The accumulators are touched
-//    by the MFMAs only (no per-stage fp32 fold), so the compiler may keep
-//    them in the accumulation registers and every dequantized weight feeds
-//    MBW MFMAs.
-//  * Group scales multiply the dequantized fp16 weights: (q - 8) is exact
-//    (the paper's magic number, Section 3.4 "Dequantization and Tensor
-//    Cores": the code ORed into 1024.0, minus 1032; the upper nibble gives
-//    1024 + 16q, fixed by one exact fma), then one fp16 multiply by s per two
-//    weights, rounded once ("Groups and Instruction Ordering": scales applied
-//    to the weights before the matrix product).  Per-channel scales multiply
-//    the final fp32 sums.
-//  * Weights stream from HBM straight into a P-deep register ring per wave
-//    (16-byte non-temporal loads; a wave's weights are its own, so nothing
-//    is gained by staging them in LDS).  The activation block of a stage
-//    (16*MBW rows x 128 k) and the stage's group scales arrive by gfx950
-//    direct-to-LDS loads in a P-deep LDS ring shared by the four waves, one
-//    barrier per stage (Section 3.4 "Memory Load Pipelining"); the
-//    activation rows are XOR-swizzled so that the MFMA-operand reads of 16
-//    rows hit 16 bank groups.
-//  * Partition (whole tiles or Stream-K ranges of 128-row blocks) and the
-//    combination of shared tiles are the other kernels' (device.h).
+//  * A work-group of eight waves (two per SIMD) owns a tile of 128 rows x 256
+//    columns.  Four waves along N take one packed 64-column tile each; the two
+//    waves of a column take the halves of every 128-row block of K, so each
+//    owns 128 x 64 outputs, every converted word feeds eight MFMAs, and the
+//    tile stays as small as with four waves.  The halves are summed in LDS when
+//    a tile is done.
+//  * A stage (one 128-row block: activation rows, XOR-swizzled, packed words, a
+//    scale row per packed tile) arrives by direct-to-LDS loads in a ring of
+//    three 49 KiB slots.  One barrier per stage, between a wave's two k-steps:
+//    by then it holds the stage's operands in registers, so the slot is free,
+//    and the next stage has landed.  The first rows, words and scales of the
+//    next stage are read during the second k-step, its second rows during the
+//    first, and the refill's loads are spread over the first.
+//  * Codes are converted by the paper's magic number (exact q - 8; Section 3.4
+//    "Dequantization and Tensor Cores") and multiplied by the group scale in
+//    fp16, rounded once ("Groups and Instruction Ordering"), a quarter word
+//    after every other MFMA (1.6 vector instructions per MFMA); per-channel
+//    scales multiply the final sums.
+//  * Reads in flight never cross the loop's back edge or a branch: the compiler
+//    takes their registers as written and could move them.
+//  * Partition and combination: as tile8.hip.
+//
+// Bound: vector issue and power (the shader clock is below 2.1 GHz here).  On
+// 28672 x 8192: 1486 us at M = 4096 and 375 at 1024, against 1735 and 427 for
+// four waves with the weights in a register ring (one wave per SIMD, loads in
+// one burst per stage) and 1460 for a library fp16 GEMM at 4096; 8192 x 10240
+// at M = 300 62 us (90).
 #include <hip/hip_runtime.h>
 #include <stdio.h>
 
@@ -36,40 +39,26 @@ namespace {
 
 using namespace dev;
 
-template <int MBW, int NBW, int P>
 struct WideShape {
-    static constexpr int NW = 4;                   // waves per work-group, all along N
-    static constexpr int TR = 16 * MBW;            // rows of A per tile
-    static constexpr int kABytes = TR * 256;       // one block of A: TR rows x 128 k x 2 B
-    static constexpr int kSBytes = NW * 1024;      // the stage's group scales: 1 KiB per wave
-    static constexpr int kStage = kABytes + kSBytes;
-    static constexpr int kDmaA = TR / (4 * NW);    // 1 KiB direct-to-LDS A loads per wave and stage
-    static_assert(MBW * NBW == 32, "32 accumulator blocks per wave");
-    static_assert(NBW == 4 || NBW == 8, "one or two packed 64-column tiles per wave");
-    static_assert(kDmaA >= 1, "activation rows per wave");
-    static_assert(P >= 3 && P * kStage <= 160 * 1024 - 64, "LDS ring");
+    static constexpr int NW = 8;
+    static constexpr int WN = 4;                   // waves along N (one packed tile each); two along K
+    static constexpr int TR = 128;                 // rows of A per tile
+    static constexpr int TC = 256;                 // columns per tile
+    static constexpr int MB = 8, NB = 4;           // 16-row and 16-column blocks per wave
+    static constexpr int kABytes = TR * 256;       // a stage: TR rows x 128 k of A,
+    static constexpr int kWBytes = TC * 64;        // TC columns x 128 k of codes,
+    static constexpr int kSBytes = WN * 256;       // and a scale row per packed tile
+    static constexpr int kStage = kABytes + kWBytes + kSBytes;
+    static constexpr int kDmaA = TR / (4 * NW);    // 1 KiB direct-to-LDS loads per wave
+    static constexpr int kDmaW = TC / (16 * NW);
+    static constexpr int P = 3;
+    static_assert(P * kStage <= 160 * 1024 - 64, "LDS");
 };
 
-// Eight codes of one word -> the fp16 weights s * (q - 8), element order
-// j = 0..7 (code j in nibble (j >> 1) + 4 (j & 1)): q - 8 exactly by the
-// magic number, then one rounding of the product with the scale.
-__device__ __forceinline__ half8_t dequant_scaled(uint32_t x, half2_t s2, const DequantConsts &k)
-{
-    const half2_t sub = {(_Float16)1032.0f, (_Float16)1032.0f};
-    const half2_t mul = {(_Float16)0.0625f, (_Float16)0.0625f};
-    const half2_t add = {(_Float16)-72.0f, (_Float16)-72.0f};
-    const uint32_t y = x >> 8;
-    const half2_t r0 = (as_h2((x & k.lo) | k.ex) - sub) * s2;
-    const half2_t r1 = __builtin_elementwise_fma(as_h2((x & k.hi) | k.ex), mul, add) * s2;
-    const half2_t r2 = (as_h2((y & k.lo) | k.ex) - sub) * s2;
-    const half2_t r3 = __builtin_elementwise_fma(as_h2((y & k.hi) | k.ex), mul, add) * s2;
-    return half8_t{r0.x, r0.y, r1.x, r1.y, r2.x, r2.y, r3.x, r3.y};
-}
-
-// One quarter (codes 2q and 2q + 1) of dequant_scaled (SCALED), or of the
-// exact magic-number conversion alone (per-channel scales multiply the sums).
+// One quarter (codes 2q and 2q + 1) of a word: q - 8 exactly by the magic
+// number, times the scale (SCALED, one rounding).
 template <bool SCALED>
-__device__ __forceinline__ half2_t convert_quarter(uint32_t x, int q, half2_t s2, const DequantConsts &k)
+__device__ __forceinline__ half2_t wide_quarter(uint32_t x, int q, half2_t s2, const DequantConsts &k)
 {
     const half2_t sub = {(_Float16)1032.0f, (_Float16)1032.0f};
     const half2_t mul = {(_Float16)0.0625f, (_Float16)0.0625f};
@@ -80,24 +69,27 @@ __device__ __forceinline__ half2_t convert_quarter(uint32_t x, int q, half2_t s2
     return SCALED ? r * s2 : r;
 }
 
-template <int MBW, int NBW, int P, bool PER_CHANNEL>
-__global__ void __launch_bounds__(256, 1) w4a16_wide_kernel(GemmProblem p)
+template <bool PER_CHANNEL>
+struct EightWaves {
+    static constexpr bool per_channel = PER_CHANNEL;
+};
+
+template <int MB, int NB, int P, typename SCALES>
+__global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
 {
-    using S = WideShape<MBW, NBW, P>;
-    constexpr int NW = S::NW;
-    constexpr int TR = S::TR;
-    constexpr int kABytes = S::kABytes;
+    using S = WideShape;
+    constexpr bool PER_CHANNEL = SCALES::per_channel;
+    static_assert(MB == S::MB && NB == S::NB && P == S::P, "128 x 64 outputs per wave, three stages");
+    constexpr int TR = S::TR, NW = S::NW;
+    constexpr int kDmaA = S::kDmaA, kDmaW = S::kDmaW, kDmaS = PER_CHANNEL ? 0 : 1;
+    constexpr int kLoads = kDmaA + kDmaW + kDmaS;
     constexpr int kStage = S::kStage;
-    constexpr int kDmaA = S::kDmaA;
-    constexpr int kSL = PER_CHANNEL ? 0 : 1;           // direct-to-LDS scale loads per wave and stage
-    constexpr int kLoads = kDmaA + kSL + NBW;          // vector-memory ops per wave and stage
-    static_assert(NBW + (P - 2) * kLoads <= 63, "vmcnt range");
-    constexpr int kBlocks = NBW * MBW;                 // 16x16 output blocks per wave
+    constexpr int kOwn = NB * MB / 2;  // blocks a wave keeps after the reduction
     __shared__ __attribute__((aligned(16))) uint8_t ring[P * kStage];
-    __shared__ int flags[2];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wn = wave & 3, kg = wave >> 2;  // packed tile of the column group, half of the 128 k
     const int lg = lane >> 4;
     const DequantConsts dq = dequant_consts();
     const int KU = p.KU;
@@ -105,13 +97,19 @@ __global__ void __launch_bounds__(256, 1) w4a16_wide_kernel(GemmProblem p)
     const int wg = xcd_local_wg(blockIdx.x, grid);
     const int u0 = range_start(p, wg, grid);
     const int u1 = range_start(p, wg + 1, grid);
-    const int c_first = tile_of(p, u0);
-    const int c_last = tile_of(p, u1 - 1);
-    const int k0 = u0 - c_first * KU;
-    const int k1 = u1 - c_last * KU;
-    const int n_st = (c_first == c_last) ? (k1 - k0) : (KU - k0) + (c_last - c_first - 1) * KU + k1;
+    // The work-group's stages: its range of the shared tiles (0 .. n_shared - 1),
+    // if any, then whole tiles n_shared + wg, n_shared + wg + grid, ...
+    const int n_shared = p.units / KU;
+    const int c_end = u1 > u0 ? tile_of(p, u1 - 1) : -1;  // the range's last tile
+    const int k1 = u1 - c_end * KU;
+    const int c_begin = u1 > u0 ? tile_of(p, u0) : n_shared + wg;
+    const int k0 = u1 > u0 ? u0 - c_begin * KU : 0;
+    const int n_st = u1 - u0 + (p.tiles - n_shared) / grid * KU;
+    // The tile after c (p.tiles or more: none), and the end of tile c's segment.
+    auto next_tile = [&](int c) { return c < c_end ? c + 1 : c < n_shared ? n_shared + wg : c + grid; };
+    auto end_of = [&](int c) { return c == c_end ? k1 : c < p.tiles ? KU : 0; };
 
-    // Tile c: column group c / rg (64 * NBW * NW columns), row group c % rg (TR rows).
+    // Tile c: column group c / rg (TC columns), row group c % rg (TR rows).
     const uint32_t RG = (uint32_t)p.rg;
     auto cg_of = [&](int c) -> uint32_t { return RG == 1 ? (uint32_t)c : (uint32_t)c / RG; };
     auto row0_of = [&](int c) -> int { return RG == 1 ? 0 : (int)((uint32_t)c - cg_of(c) * RG) * TR; };
@@ -119,327 +117,382 @@ __global__ void __launch_bounds__(256, 1) w4a16_wide_kernel(GemmProblem p)
         const int r = p.M - row0_of(c);
         return r < TR ? r : TR;
     };
-    // this wave's first packed 64-column tile (NBW / 4 of them)
-    auto ptile_of = [&](int c) -> uint32_t { return (cg_of(c) * NW + (uint32_t)wave) * (uint32_t)(NBW / 4); };
+    const uint32_t n_tiles = (uint32_t)p.N / 64u;  // packed 64-column tiles
 
     // ---- per-lane address parts ----
-    const uint32_t w_lane = (uint32_t)lane * 16u;
-    const uint32_t w_next = (uint32_t)KU * 4096u;  // the next packed tile's weights
+    // A: load i of this wave brings rows r0 + lg + 16 i (all with one swizzle,
+    // so that one register and a scalar step address every load)
+    const int r0_dma = (wave & 3) * 4 + (wave >> 2) * (kDmaA * 16);
+    const uint32_t a_dma =
+        (uint32_t)((r0_dma + lg) * p.K + (((lane & 15) ^ ((r0_dma + lg) & 15)) * 8)) * 2u;
+    const uint32_t a_rows16 = (uint32_t)p.K * 32u;
+    // this wave's weight loads: KiB kDmaW * wave .. of the stage's TC / 16 (four per packed tile)
+    const uint32_t w_pt = (uint32_t)(kDmaW * wave) >> 2;
+    const uint32_t w_lane = (uint32_t)lane * 16u + (((uint32_t)(kDmaW * wave) & 3u) << 10);
+    // the scale row of this wave's packed tile (its 128 bytes twice)
+    const uint32_t s_pt = (uint32_t)wn;
+    const uint32_t s_lane = (uint32_t)(lane & 31) * 4u;
     const uint32_t w_bytes = (uint32_t)p.K * (uint32_t)(p.N / 2);
     const uint32_t s_bytes = (uint32_t)p.G * (uint32_t)p.N * 2u;
-    // A: load i of this wave brings rows r = wave*TR/4 + 4i + lg, lane chunk
-    // (lane % 16) of row r holding the global chunk (lane % 16) ^ (r % 16)
-    uint32_t a_dma[kDmaA];
-#pragma unroll
-    for (int i = 0; i < kDmaA; ++i) {
-        const int r = wave * (TR / NW) + 4 * i + lg;
-        a_dma[i] = (uint32_t)(r * p.K + (((lane & 15) ^ (r & 15)) * 8)) * 2u;
-    }
-    // scales: lane L % 16 brings 16 bytes of its wave's scale run: packed tile
-    // (L % 16) / 8 (NBW = 8; else 0), chunk L % 8 of the 128-byte row; the
-    // other lanes repeat those loads
-    const uint32_t s_lane =
-        (NBW == 8 ? (uint32_t)((lane & 15) >> 3) * (uint32_t)p.G * 128u : 0u) + (uint32_t)(lane & 7) * 16u;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)ring;
-    // MFMA operand reads: row mb*16 + (lane % 16), chunk (4t + lg) ^ (lane % 16)
-    uint32_t a_rd[4];
+    // Operand reads, k-step 2 kg + t of the block: row l % 16 of a 16-row
+    // block, chunk (4 (2 kg + t) + l / 16) ^ (l % 16).  A wave's row block mb
+    // is row block (mb + 4 kg) % 8 of the tile, so that the blocks it keeps
+    // after the reduction are its first four.
+    uint32_t a_rd[2][2];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) a_rd[t] = lds0 + (uint32_t)((lane & 15) * 256 + (((4 * t + lg) ^ (lane & 15)) << 4));
-    // this lane's column scale of block nb: packed tile nb / 4, byte
-    // (cn / 4) * 32 + ((nb % 4) * 4 + cn % 4) * 2 of its 128-byte row, cn = lane % 16
-    const uint32_t s_rd = lds0 + (uint32_t)(kABytes + wave * 1024 + ((lane & 15) >> 2) * 32 + (lane & 3) * 2);
-
-    u32x4_t wr[P][NBW];
+    for (int t = 0; t < 2; ++t) {
+        const uint32_t at =
+            lds0 + (uint32_t)((lane & 15) * 256) + (uint32_t)(((4 * (2 * kg + t) + lg) ^ (lane & 15)) << 4);
+        a_rd[t][0] = at + (uint32_t)kg * 16384u;
+        a_rd[t][1] = at + (uint32_t)(1 - kg) * 16384u;
+    }
+    const uint32_t w_rd = lds0 + (uint32_t)(S::kABytes + wn * 4096 + lane * 16 + kg * 8);
+    // this lane's column scale of block nb: byte (cn / 4) * 32 + (nb * 4 + cn % 4) * 2 of the row, cn = lane % 16
+    const uint32_t s_rd =
+        lds0 + (uint32_t)(S::kABytes + S::kWBytes + wn * 256 + ((lane & 15) >> 2) * 32 + (lane & 3) * 2);
 
     // ---- load cursor ----
-    int ld_c = c_first, ld_ku = k0;
-    int ld_end = (c_first == c_last) ? k1 : KU;
-    uint32_t ld_w = (ptile_of(ld_c) * (uint32_t)KU + (uint32_t)ld_ku) << 12;
-    uint32_t ld_s = ptile_of(ld_c) * (uint32_t)p.G * 128u;
-    const uint16_t *ld_a = p.A + (int64_t)row0_of(ld_c) * p.K;
-    uint32_t a_bytes = (uint32_t)rows_of(ld_c) * (uint32_t)p.K * 2u;
-    const uint32_t a_dst0 = lds0 + (uint32_t)(wave * (TR / NW) * 256);
-    const uint32_t s_dst0 = lds0 + (uint32_t)(kABytes + wave * 1024);
-
-    auto issue = [&](int j) {
-        const bool on = ld_ku < ld_end;
-        uint32_t a_base = a_dst0, s_base = s_dst0;
-        asm volatile("" : "+s"(a_base), "+s"(s_base));
-        {  // activation rows, then the scales: the stage's direct-to-LDS loads
+    int ld_c = c_begin, ld_ku = k0;
+    int ld_end = end_of(ld_c);
+    uint32_t ld_slot = 0;  // byte offset of the ring slot
+    uint32_t ld_w, ld_wbytes, ld_s, ld_sbytes, a_bytes;
+    const uint16_t *ld_a;
+    auto ld_tile = [&]() {
+        const uint32_t pt0 = cg_of(ld_c) * (uint32_t)(S::TC / 64);
+        const bool in = ld_end > 0;
+        ld_w = (pt0 + w_pt) * (uint32_t)KU << 12;
+        ld_wbytes = in && pt0 + w_pt < n_tiles ? w_bytes : 0u;
+        ld_s = (pt0 + s_pt) * (uint32_t)p.G << 7;
+        ld_sbytes = in && pt0 + s_pt < n_tiles ? s_bytes : 0u;
+        const int c = in ? ld_c : 0;
+        ld_a = p.A + (int64_t)row0_of(c) * p.K;
+        a_bytes = in ? (uint32_t)rows_of(c) * (uint32_t)p.K * 2u : 0u;
+    };
+    ld_tile();
+    // Load i of a stage (0 .. kLoads - 1), all direct to LDS.
+    auto issue = [&](int i) {
+        uint32_t slot = lds0 + ld_slot;
+        asm volatile("" : "+s"(slot));
+        if (i < kDmaA) {
             const __amdgpu_buffer_rsrc_t ra =
-                __builtin_amdgcn_make_buffer_rsrc((void *)ld_a, (short)0, on ? a_bytes : 0u, kBufferFlags);
-            const uint32_t dst = a_base + (uint32_t)(j * kStage);
-#pragma unroll
-            for (int i = 0; i < kDmaA; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    ra, (__attribute__((address_space(3))) void *)(uintptr_t)(dst + (uint32_t)(i * 1024)), 16,
-                    (int)a_dma[i], ld_ku * 256, 0, 0);
-            if constexpr (!PER_CHANNEL) {
-                const __amdgpu_buffer_rsrc_t rs =
-                    __builtin_amdgcn_make_buffer_rsrc((void *)p.S, (short)0, on ? s_bytes : 0u, kBufferFlags);
-                const uint32_t s_off = ld_s + ((uint32_t)scale_row_of(ld_ku, p) << 7);
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rs, (__attribute__((address_space(3))) void *)(uintptr_t)(s_base + (uint32_t)(j * kStage)), 16,
-                    (int)s_lane, (int)s_off, 0, 0);
-            }
+                __builtin_amdgcn_make_buffer_rsrc((void *)ld_a, (short)0, a_bytes, kBufferFlags);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                ra,
+                (__attribute__((address_space(3))) void *)(uintptr_t)(slot + (uint32_t)(r0_dma * 256 + i * 4096)),
+                16, (int)(a_dma + (uint32_t)i * a_rows16), ld_ku * 256, 0, 0);
+        } else if (i < kDmaA + kDmaW) {
+            const __amdgpu_buffer_rsrc_t rw =
+                __builtin_amdgcn_make_buffer_rsrc((void *)p.W, (short)0, ld_wbytes, kBufferFlags);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rw,
+                (__attribute__((address_space(3))) void *)(uintptr_t)(
+                    slot + (uint32_t)(S::kABytes + (wave * kDmaW + i - kDmaA) * 1024)),
+                16, (int)(w_lane + (uint32_t)(i - kDmaA) * 1024u), (int)(ld_w + ((uint32_t)ld_ku << 12)), 0,
+                kAuxNonTemporal);
+        } else if (i < kLoads) {
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)p.S, (short)0, ld_sbytes, kBufferFlags);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs,
+                (__attribute__((address_space(3))) void *)(uintptr_t)(
+                    slot + (uint32_t)(S::kABytes + S::kWBytes + wn * 256)),
+                4, (int)s_lane, (int)(ld_s + ((uint32_t)scale_row_of(ld_ku, p) << 7)), 0, 0);
         }
-        issue_order_point();  // the direct-to-LDS loads are the stage's oldest
-        const __amdgpu_buffer_rsrc_t rw =
-            __builtin_amdgcn_make_buffer_rsrc((void *)p.W, (short)0, on ? w_bytes : 0u, kBufferFlags);
-#pragma unroll
-        for (int b = 0; b < NBW; ++b)
-            wr[j][b] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                                                       rw, w_lane + (b & 3) * 1024, ld_w + (b >> 2) * w_next,
-                                                       kAuxNonTemporal));
-        issue_order_point();  // stages do not interleave
+        issue_order_point();
     };
     auto advance_ld = [&]() {
-        ld_ku += 1;
-        ld_w += 4096u;
-        if (ld_ku >= ld_end) {  // next tile
-            ld_c += 1;
+        ld_slot = ld_slot == (uint32_t)((P - 1) * kStage) ? 0u : ld_slot + (uint32_t)kStage;
+        if (++ld_ku >= ld_end) {
+            ld_c = next_tile(ld_c);
             ld_ku = 0;
-            ld_end = (ld_c < c_last) ? KU : (ld_c == c_last) ? k1 : 0;  // 0: past the range
-            ld_w = (ptile_of(ld_c) * (uint32_t)KU) << 12;
-            ld_s = ptile_of(ld_c) * (uint32_t)p.G * 128u;
-            if (ld_end > 0) {
-                ld_a = p.A + (int64_t)row0_of(ld_c) * p.K;
-                a_bytes = (uint32_t)rows_of(ld_c) * (uint32_t)p.K * 2u;
-            }
+            ld_end = end_of(ld_c);
+            ld_tile();
         }
     };
 
 #pragma unroll
-    for (int j = 0; j < P - 1; ++j) {
-        issue(j);
+    for (int j = 0; j < P; ++j) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) issue(i);
         advance_ld();
     }
 
-    float4_t acc[NBW][MBW];
+    float4_t acc[NB][MB];
     const float4_t zero4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int b = 0; b < NBW; ++b)
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int mb = 0; mb < MBW; ++mb) acc[b][mb] = zero4;
+        for (int mb = 0; mb < MB; ++mb) acc[b][mb] = zero4;
 
-    // One stage (ring slot j): the column scales first (group scales), then
-    // per k-step the MBW activation operands (read one k-step ahead) and, per
-    // column block, one dequantized word feeding MBW MFMAs.
-    auto compute = [&](int j) {
-        uint32_t sv[PER_CHANNEL ? 1 : NBW];
+    u32x4_t av[2][MB];                   // [k-step][row block]
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    u32x2_t wv[NB];                      // packed words, k-step in the element
+    uint32_t sv[NB];                     // column scales as read
+    half2_t s2[NB];
+    half2_t nx[4];                       // converted operand of the next eight MFMAs
+    uint32_t rd_slot = 0;
+    auto read_a = [&](int t, int mb) {
+        asm volatile("ds_read_b128 %0, %1 offset:%2"
+                     : "=v"(av[t][mb])
+                     : "v"(a_rd[t][mb >> 2] + rd_slot), "i"((mb & 3) * 4096));
+    };
+    auto read_w = [&](int b) {
+        asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(wv[b]) : "v"(w_rd + rd_slot), "i"(b * 1024));
+    };
+    auto read_s = [&](int b) {
+        asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(sv[b]) : "v"(s_rd + rd_slot), "i"(b * 8));
+    };
+    auto landed_a = [&](int t) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(av[t][mb]));
+    };
+    auto landed_ws = [&]() {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            asm volatile("" : "+v"(wv[b]));
+            if constexpr (!PER_CHANNEL) asm volatile("" : "+v"(sv[b]));
+        }
+    };
+    auto scales = [&]() {
         if constexpr (!PER_CHANNEL) {
 #pragma unroll
-            for (int b = 0; b < NBW; ++b)
-                asm volatile("ds_read_u16 %0, %1 offset:%2"
-                             : "=v"(sv[b])
-                             : "v"(s_rd + (uint32_t)(j * kStage)), "i"((b >> 2) * 128 + (b & 3) * 8));
-        }
-        u32x4_t a[2][MBW];
-        auto read_a = [&](int t, u32x4_t (&dst)[MBW]) {
-#pragma unroll
-            for (int mb = 0; mb < MBW; ++mb)
-                asm volatile("ds_read_b128 %0, %1 offset:%2"
-                             : "=v"(dst[mb])
-                             : "v"(a_rd[t] + (uint32_t)(j * kStage)), "i"(mb * 4096));
-        };
-        read_a(0, a[0]);
-        half2_t s2[NBW] = {};  // group scales (unused with per-channel scales)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            u32x4_t(&cur)[MBW] = a[t & 1];
-            // this k-step's operands (and at t = 0 the scales) are complete;
-            // the next step's reads are issued before its MFMAs so that they
-            // overlap them.  The empty asm "redefines" what the wait made
-            // available, so no use is scheduled before it.
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int mb = 0; mb < MBW; ++mb) asm volatile("" : "+v"(cur[mb]));
-            if constexpr (!PER_CHANNEL) {
-                if (t == 0) {
-#pragma unroll
-                    for (int b = 0; b < NBW; ++b) {
-                        asm volatile("" : "+v"(sv[b]));
-                        s2[b] = as_h2(sv[b] | (sv[b] << 16));
-                    }
-                }
-            }
-            if (t < 3) read_a(t + 1, a[(t + 1) & 1]);
-            // Column block b's MFMAs are interleaved with the conversion of
-            // block b + 1's word, one quarter after every other MFMA: the
-            // conversion does not depend on the MFMAs, so the SIMD issues
-            // it while the matrix core works (the wave issues in order, so
-            // a run of MFMAs would hold back the conversion behind them).
-            half2_t nx[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) nx[q] = convert_quarter<!PER_CHANNEL>(wr[j][0][t], q, s2[0], dq);
-#pragma unroll
-            for (int b = 0; b < NBW; ++b) {
-                const half8_t w = {nx[0].x, nx[0].y, nx[1].x, nx[1].y, nx[2].x, nx[2].y, nx[3].x, nx[3].y};
-#pragma unroll
-                for (int mb = 0; mb < MBW; ++mb) {
-                    acc[b][mb] = mfma(w, __builtin_bit_cast(half8_t, cur[mb]), acc[b][mb]);
-                    constexpr int kStep = MBW / 4;  // MFMAs per quarter
-                    if (b + 1 < NBW && mb % kStep == 0)
-                        nx[mb / kStep] = convert_quarter<!PER_CHANNEL>(wr[j][b + 1][t], mb / kStep,
-                                                                       s2[b + 1], dq);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
+            for (int b = 0; b < NB; ++b) s2[b] = as_h2(sv[b] | (sv[b] << 16));
         }
     };
+    // The MFMA of k-step t, column block b and row block mb; every other one
+    // also converts a quarter of the next operand's word
+    auto slot = [&](int t, int b, int mb, half8_t w, uint32_t next, half2_t ns) {
+        acc[b][mb] = mfma(w, __builtin_bit_cast(half8_t, av[t][mb]), acc[b][mb]);
+        if ((mb & 1) == 0) nx[mb >> 1] = wide_quarter<!PER_CHANNEL>(next, mb >> 1, ns, dq);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto operand = [&]() {
+        return half8_t{nx[0].x, nx[0].y, nx[1].x, nx[1].y, nx[2].x, nx[2].y, nx[3].x, nx[3].y};
+    };
 
-    // block j of this wave = column block j / MBW, row block j % MBW; slot index wave*kBlocks + j
-    auto own = [&](int j) { return wave * kBlocks + j; };
+    // block j of this wave after the reduction = column block j / 4, row block 4 kg + j % 4
+    auto own = [&](int j) { return wave * kOwn + j; };
     auto store_c = [&](int c, const float4_t *out) {
-        const int r0 = row0_of(c), rows = rows_of(c);
-        const uint32_t pt = ptile_of(c);
-        half8_t cs[NBW / 4][2];
-        if constexpr (PER_CHANNEL) {
-            // the output lane's 16 column scales of each packed tile (32 bytes)
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));  // addresses formed here, not held across the loop
+        const int lg = lane >> 4;
+        const int r0 = row0_of(c) + kg * 64, rows = rows_of(c) - kg * 64;
+        const uint32_t pt = cg_of(c) * 4u + (uint32_t)wn;
+        if (pt >= n_tiles) return;
 #pragma unroll
-            for (int i = 0; i < NBW / 4; ++i) {
-                const _Float16 *src = (const _Float16 *)p.S + (int64_t)(pt + i) * 64 + lg * 16;
-                cs[i][0] = *(const half8_t *)src;
-                cs[i][1] = *(const half8_t *)(src + 8);
-            }
-        }
+        for (int b = 0; b < NB; ++b) {
+            half4_t cs = {};
+            if constexpr (PER_CHANNEL) cs = *(const half4_t *)(p.S + (int64_t)pt * 64 + lg * 16 + b * 4);
 #pragma unroll
-        for (int jb = 0; jb < kBlocks; ++jb) {
-            const int b = jb / MBW, mb = jb % MBW;
-            const int m = mb * 16 + (lane & 15);
-            if (m < rows) {
-                float4_t vv = out[jb];
-                if constexpr (PER_CHANNEL) {
-                    const int e = (b & 3) * 4;
+            for (int mb = 0; mb < 4; ++mb) {
+                const int m = mb * 16 + (lane & 15);
+                if (m < rows) {
+                    float4_t vv = out[b * 4 + mb];
+                    if constexpr (PER_CHANNEL) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) vv[i] *= (float)cs[b >> 2][e >> 3][(e & 7) + i];
+                        for (int i = 0; i < 4; ++i) vv[i] *= (float)cs[i];
+                    }
+                    const half4_t h = {(_Float16)vv[0], (_Float16)vv[1], (_Float16)vv[2], (_Float16)vv[3]};
+                    *(half4_t *)(p.C + (int64_t)(r0 + m) * p.N + (int64_t)(pt * 64 + b * 16 + lg * 4)) = h;
                 }
-                const half4_t h = {(_Float16)vv[0], (_Float16)vv[1], (_Float16)vv[2], (_Float16)vv[3]};
-                *(half4_t *)(p.C + (int64_t)(r0 + m) * p.N + (int64_t)(pt * 64 + b * 16 + lg * 4)) = h;
             }
         }
     };
-
-    const int slot_floats = NW * kBlocks * 256;
-    float *const my_slots = p.partials + (int64_t)wg * 2 * slot_floats;  // slot 0; slot 1 follows
-    bool has_first = false, has_last = false;
-
-    int cp_c = c_first, cp_ku = k0, cp_begin = k0;
-    int cp_end = (c_first == c_last) ? k1 : KU;
-    // A segment is complete: write C (whole tile) or slot 0 (shared first
-    // tile).  A shared last tile stays in acc; it is combined after the loop.
-    auto finish_segment = [&]() {
-        const bool partial = cp_begin != 0 || cp_end != KU;
-        if (partial && cp_c == c_last) {
-            has_last = true;
-            return;
-        }
-        float4_t out[kBlocks];
+    constexpr int kSlotFloats = NW * kOwn * 256;
+    float *const my_slots = p.partials + (int64_t)wg * 2 * kSlotFloats;
+    bool reduce_first = false, reduce_last = false;  // this wave sums that tile at the end
+    int cp_c = c_begin, cp_ku = k0, cp_begin = k0;
+    int cp_end = end_of(cp_c);
+    // Sum the two K halves' tiles: wave (wn, kg) keeps row blocks 4 kg ..
+    // 4 kg + 3 and gives the others to its partner, through ring slot `at`
+    // (free: every wave holds its stage's operands in registers, and the slot's
+    // refill is issued after this), four rounds of 4 KiB per wave.
+    auto reduce_halves = [&](uint32_t at) {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        float4_t *const mine = reinterpret_cast<float4_t *>(ring + at + (uint32_t)wave * 4096u);
+        const float4_t *const theirs = reinterpret_cast<const float4_t *>(ring + at + (uint32_t)(wave ^ 4) * 4096u);
 #pragma unroll
-        for (int jb = 0; jb < kBlocks; ++jb) {
-            out[jb] = acc[jb / MBW][jb % MBW];
-            acc[jb / MBW][jb % MBW] = zero4;
-        }
-        if (partial) {
-            has_first = true;
+        for (int b = 0; b < NB; ++b) {
 #pragma unroll
-            for (int jb = 0; jb < kBlocks; ++jb) store_partial(my_slots, own(jb), lane, out[jb]);
+            for (int mb = 0; mb < 4; ++mb) mine[mb * 64 + lane] = acc[b][4 + mb];
+            lds_barrier();
+#pragma unroll
+            for (int mb = 0; mb < 4; ++mb) acc[b][mb] += theirs[mb * 64 + lane];
+            lds_barrier();
+        }
+    };
+    // A segment other than the last is complete: write C (whole tile), or the
+    // slot of the range's last (1) or first (0) tile, and arrive at the tile.
+    auto finish_segment = [&](uint32_t at) {
+        reduce_halves(at);
+        float4_t out[kOwn];
+#pragma unroll
+        for (int j = 0; j < kOwn; ++j) out[j] = acc[j / 4][j % 4];
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) acc[b][mb] = zero4;
+        if (cp_begin != 0 || cp_end != KU) {
+            int l = lane;
+            asm volatile("" : "+v"(l));
+            float *const slot = my_slots + (cp_c == c_end ? kSlotFloats : 0);
+#pragma unroll
+            for (int j = 0; j < kOwn; ++j) store_partial16(slot, own(j), l, out[j]);
+            wait_vmcnt<0>();
+            const bool last = arrive_by_wave(p, cp_c, wave, grid, l);
+            if (cp_c == c_end)
+                reduce_last = last;
+            else
+                reduce_first = last;
         } else {
             store_c(cp_c, out);
         }
     };
 
-    // Stage st (ring slot j) with `later` stages issued after it; `refill`:
-    // the slot of stage st - 1 takes stage st + P - 1.  The wait covers this
-    // wave's direct-to-LDS loads of the stage (issued before its own weight
-    // loads and the later stages'; vector-memory operations complete in
-    // order); the barrier makes every wave's loads of the stage visible and
-    // frees the slot of stage st - 1.  Loads are issued unconditionally (past
-    // the range through empty descriptors, into a slot no wave reads again)
-    // so that every stage has the same load pattern.
-    auto step = [&](int j, int st, int later, bool refill) {
-        const bool live = st < n_st;
-        if (live) {
-            wait_vmcnt_n(NBW + later * kLoads);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        }
-        if (refill) {
-            issue((j + P - 1) % P);
-            advance_ld();
-        }
-        if (live) {
-            compute(j);
-            if (cp_ku + 1 >= cp_end) {
-                finish_segment();
-                cp_c += 1;
-                cp_ku = 0;
-                cp_begin = 0;
-                cp_end = (cp_c < c_last) ? KU : k1;
-            } else {
-                cp_ku += 1;
+    // Stage 0's operands.
+    wait_vmcnt<(P - 1) * kLoads>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) read_a(t, mb);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        read_w(b);
+        if constexpr (!PER_CHANNEL) read_s(b);
+    }
+    wait_lgkmcnt0();
+    landed_a(0);
+    landed_a(1);
+    landed_ws();
+    scales();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) nx[q] = wide_quarter<!PER_CHANNEL>(wv[0][0], q, s2[0], dq);
+    // first k-step of stage 0
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const half8_t w = operand();
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+            slot(0, b, mb, w, b + 1 < NB ? wv[b + 1][0] : wv[0][1], s2[(b + 1) % NB]);
+    }
+
+    for (int st = 0; st + 1 < n_st; ++st) {
+        // Stage st + 1 has landed (P - 2 stages were issued after it), and
+        // every wave holds the rest of stage st in registers.
+        wait_lgkmcnt0();
+        wait_vmcnt<(P - 2) * kLoads>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        landed_a(1);
+        const uint32_t old_slot = rd_slot;
+        rd_slot = rd_slot == (uint32_t)((P - 1) * kStage) ? 0u : rd_slot + (uint32_t)kStage;
+        // second k-step of stage st; reads stage st + 1's first rows, words and scales
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const half8_t w = operand();
+            if (b == NB - 1) {
+                wait_lgkmcnt_n(1);  // all but word 3
+                landed_a(0);
+                landed_ws();
+                scales();
+            }
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                slot(1, b, mb, w, b + 1 < NB ? wv[b + 1][1] : wv[0][0], s2[(b + 1) % NB]);
+                const int k = b * MB + mb;
+                if (k < MB) read_a(0, k);
+                else if (!PER_CHANNEL && k < MB + NB) read_s(k - MB);
+                // word b' is free once its last quarter is converted, one block ahead of its MFMAs
+                if (mb == 7 && b < 2) read_w(b);
+                if (mb == 2 && b == 2) read_w(2);
+                if (mb == 7 && b == 2) read_w(3);
             }
         }
-    };
-    const int st_last = (n_st - 1) / P * P;
-    for (int st0 = 0; st0 < st_last; st0 += P) {
+        wait_lgkmcnt0();
+        asm volatile("" : "+v"(wv[NB - 1]));
+        // stage st was its segment's last?
+        if (cp_ku + 1 >= cp_end) {
+            finish_segment(old_slot);
+            cp_c = next_tile(cp_c);
+            cp_ku = 0;
+            cp_begin = 0;
+            cp_end = end_of(cp_c);
+        } else {
+            cp_ku += 1;
+        }
+        // first k-step of stage st + 1; refills stage st's slot and reads the second k-step's rows
 #pragma unroll
-        for (int j = 0; j < P; ++j) step(j, st0 + j, P - 2, true);
+        for (int b = 0; b < NB; ++b) {
+            const half8_t w = operand();
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) {
+                slot(0, b, mb, w, b + 1 < NB ? wv[b + 1][0] : wv[0][1], s2[(b + 1) % NB]);
+                const int k = b * MB + mb;
+                if (k < MB) read_a(1, k);
+                if (k % 4 == 1 && k / 4 < kLoads) issue(k / 4);
+            }
+        }
+        advance_ld();
     }
+    wait_lgkmcnt0();
+    landed_a(1);
+    // second k-step of the last stage
 #pragma unroll
-    for (int j = 0; j < P; ++j) step(j, st_last + j, j == 0 ? P - 2 : P - 1 - j, j == 0);
-
-    float4_t last_out[kBlocks];
+    for (int b = 0; b < NB; ++b) {
+        const half8_t w = operand();
 #pragma unroll
-    for (int jb = 0; jb < kBlocks; ++jb) last_out[jb] = acc[jb / MBW][jb % MBW];
-    auto own_slot = [&](int jb) { return own(jb); };
-    combine_tiles<kBlocks>(p, flags, wg, grid, slot_floats, lane, has_first, c_first, has_last, c_last, last_out,
-                           own_slot, store_c);
-}
+        for (int mb = 0; mb < MB; ++mb) slot(1, b, mb, w, wv[b + 1 < NB ? b + 1 : b][1], s2[b + 1 < NB ? b + 1 : b]);
+    }
+    wait_vmcnt<0>();
+    lds_barrier();
+    reduce_halves(0);
 
-template <int MBW, int NBW, int P>
-hipError_t launch_wide(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream)
-{
-    GemmProblem arg = p;
-    void *args[] = {&arg};
-    const void *fn = (p.group_units == 0) ? (const void *)&w4a16_wide_kernel<MBW, NBW, P, true>
-                                          : (const void *)&w4a16_wide_kernel<MBW, NBW, P, false>;
-    return hipLaunchKernel(fn, dim3(cfg.grid), dim3(256), args, 0, stream);
-}
-
-// Ring depth per shape: what the LDS holds (64-row tiles: 20 KiB per stage;
-// 128-row tiles: 36 KiB) and the register ring affords (NBW words of 16
-// bytes per lane and stage).
-template <int MBW, int NBW>
-constexpr int wide_depth()
-{
-    return MBW == 4 ? 3 : 4;
+    float4_t last_out[kOwn];
+#pragma unroll
+    for (int j = 0; j < kOwn; ++j) last_out[j] = acc[j / 4][j % 4];
+    // The last segment: whole, or the range's last tile (shared), whose sums
+    // this wave adds from its registers if it completes the tile.
+    float4_t out[kOwn];
+    if (cp_begin == 0 && cp_end == KU) {
+        store_c(cp_c, last_out);
+    } else {
+#pragma unroll
+        for (int j = 0; j < kOwn; ++j) store_partial16(my_slots + kSlotFloats, own(j), lane, last_out[j]);
+        wait_vmcnt<0>();
+        if (arrive_by_wave(p, cp_c, wave, grid, lane)) {
+            reduce_by_wave<kOwn>(p, cp_c, grid, kSlotFloats, lane, own, wg, last_out, out);
+            store_c(cp_c, out);
+        }
+    }
+    if (reduce_first) {
+        reduce_by_wave<kOwn>(p, c_begin, grid, kSlotFloats, lane, own, -1, last_out, out);
+        store_c(c_begin, out);
+    }
+    if (reduce_last) {
+        reduce_by_wave<kOwn>(p, c_end, grid, kSlotFloats, lane, own, -1, last_out, out);
+        store_c(c_end, out);
+    }
 }
 
 }  // namespace
 
 hipError_t launch_wide_gemm(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream)
 {
-    switch (cfg.mb * 10 + cfg.nb) {
-    case 48: return launch_wide<4, 8, wide_depth<4, 8>()>(cfg, p, stream);
-    case 84: return launch_wide<8, 4, wide_depth<8, 4>()>(cfg, p, stream);
-    default: return hipErrorInvalidValue;
-    }
+    if (cfg.mb != 8 || cfg.nb != 4) return hipErrorInvalidValue;
+    GemmProblem arg = p;
+    void *args[] = {&arg};
+    const void *fn = (p.group_units == 0) ? (const void *)&w4a16_wide_kernel<8, 4, 3, EightWaves<true>>
+                                          : (const void *)&w4a16_wide_kernel<8, 4, 3, EightWaves<false>>;
+    return hipLaunchKernel(fn, dim3(cfg.grid), dim3(512), args, 0, stream);
 }
 
-void wide_kernel_name(const GemmConfig &cfg, bool per_channel, char *buf, size_t n)
+void wide_kernel_name(bool per_channel, char *buf, size_t n)
 {
-    int d = 0;
-    switch (cfg.mb * 10 + cfg.nb) {
-    case 48: d = wide_depth<4, 8>(); break;
-    case 84: d = wide_depth<8, 4>(); break;
-    default: break;
-    }
-    if (!d) {
-        if (n) buf[0] = 0;
-        return;
-    }
-    snprintf(buf, n, "w4a16_wide_kernel<%d, %d, %d, %s>", cfg.mb, cfg.nb, d, per_channel ? "true" : "false");
+    snprintf(buf, n, "w4a16_wide_kernel<8, 4, 3, EightWaves<%s>>", per_channel ? "true" : "false");
 }
 
 }  // namespace marlin
