@@ -23,50 +23,101 @@ namespace {
 
 __device__ __forceinline__ int nibble_of(int j) { return (j >> 1) + 4 * (j & 1); }
 
-__global__ void pack_weights_kernel(const uint8_t *__restrict__ q, int K, int N,
-                                    uint32_t *__restrict__ w)
+// A thread takes four adjacent columns over the 32 rows 32t + 8lg + j (t, j) of
+// one 128-row block: a row is one dword of four codes, so 16 lanes read 64
+// bytes of a row and a wave four octets of rows, and the thread's words are four
+// 16-byte vectors (t = 0..3) of adjacent lanes of the packed layout.  Rows j and
+// j + 2 share a byte (v_lshl_or), then a 4 x 4 byte transpose gives the columns'
+// words.  Bound by memory: 8192 x 28672 in 85 us, either way (one thread per
+// word, eight byte accesses each: 176 us packing, 239 unpacking).
+// (q may have any alignment: callers pass views of larger buffers)
+__device__ __forceinline__ uint32_t load_codes(const uint8_t *p)
 {
-    const int64_t words = (int64_t)K * N / 8;
-    const int KU = K / 128;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < words;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int t = (int)(idx & 3);
-        const int l = (int)((idx >> 2) & 63);
-        const int nb = (int)((idx >> 8) & 3);
-        const int64_t tile = idx >> 10;  // c*KU + ku
-        const int ku = (int)(tile % KU);
-        const int c = (int)(tile / KU);
-        const int n = 64 * c + 16 * nb + (l & 15);
-        const int k0 = 128 * ku + 32 * t + 8 * (l >> 4);
-        uint32_t word = 0;
+    uint32_t v;
+    __builtin_memcpy(&v, p, 4);
+    return v;
+}
+
+struct PackItem {
+    int64_t src;  // byte index of row 8lg of the block, first column
+    int64_t dst;  // word index of the first column's t = 0
+};
+
+__device__ __forceinline__ PackItem pack_item(int64_t item, int N, int KU)
+{
+    const int n4 = (int)(item & 15);         // four columns of the 64
+    const int lg = (int)((item >> 4) & 3);
+    const int64_t unit = item >> 6;          // ku fastest over column tiles: consecutive units read adjacent bytes
+    const int tiles = N / 64;
+    const int c = (int)(unit % tiles);
+    const int ku = (int)(unit / tiles);
+    const int n = 4 * n4;
+    return {((int64_t)ku * 128 + 8 * lg) * N + 64 * c + n,
+            ((((int64_t)c * KU + ku) * 4 + (n >> 4)) * 64 + lg * 16 + (n & 15)) * 4};
+}
+
+__global__ void __launch_bounds__(256) pack_weights_kernel(const uint8_t *__restrict__ q, int K, int N,
+                                                           uint32_t *__restrict__ w)
+{
+    const int64_t items = (int64_t)K * N / 128;
+    for (int64_t item = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; item < items;
+         item += (int64_t)gridDim.x * blockDim.x) {
+        const PackItem it = pack_item(item, N, K / 128);
+        uint32_t d[4][8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t code = q[(int64_t)(k0 + j) * N + n] & 0xFu;
-            word |= code << (4 * nibble_of(j));
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) d[t][j] = load_codes(q + it.src + (int64_t)(32 * t + j) * N);
+        uint32_t word[4][4];  // [column][t]
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            constexpr uint32_t m = 0x0F0F0F0Fu;
+            // byte c: codes (j, j + 2) of column c in its low and high nibble
+            const uint32_t x = (d[t][0] & m) | (d[t][2] & m) << 4, y = (d[t][4] & m) | (d[t][6] & m) << 4;
+            const uint32_t u = (d[t][1] & m) | (d[t][3] & m) << 4, v = (d[t][5] & m) | (d[t][7] & m) << 4;
+            const uint32_t xy0 = __builtin_amdgcn_perm(y, x, 0x05010400u), xy1 = __builtin_amdgcn_perm(y, x, 0x07030602u);
+            const uint32_t uv0 = __builtin_amdgcn_perm(v, u, 0x05010400u), uv1 = __builtin_amdgcn_perm(v, u, 0x07030602u);
+            word[0][t] = __builtin_amdgcn_perm(uv0, xy0, 0x05040100u);
+            word[1][t] = __builtin_amdgcn_perm(uv0, xy0, 0x07060302u);
+            word[2][t] = __builtin_amdgcn_perm(uv1, xy1, 0x05040100u);
+            word[3][t] = __builtin_amdgcn_perm(uv1, xy1, 0x07060302u);
         }
-        w[idx] = word;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *(uint4 *)(w + it.dst + 4 * i) = make_uint4(word[i][0], word[i][1], word[i][2], word[i][3]);
     }
 }
 
-__global__ void unpack_weights_kernel(const uint32_t *__restrict__ w, int K, int N,
-                                      uint8_t *__restrict__ q)
+__global__ void __launch_bounds__(256) unpack_weights_kernel(const uint32_t *__restrict__ w, int K, int N,
+                                                             uint8_t *__restrict__ q)
 {
-    const int64_t words = (int64_t)K * N / 8;
-    const int KU = K / 128;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < words;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int t = (int)(idx & 3);
-        const int l = (int)((idx >> 2) & 63);
-        const int nb = (int)((idx >> 8) & 3);
-        const int64_t tile = idx >> 10;
-        const int ku = (int)(tile % KU);
-        const int c = (int)(tile / KU);
-        const int n = 64 * c + 16 * nb + (l & 15);
-        const int k0 = 128 * ku + 32 * t + 8 * (l >> 4);
-        const uint32_t word = w[idx];
+    const int64_t items = (int64_t)K * N / 128;
+    for (int64_t item = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; item < items;
+         item += (int64_t)gridDim.x * blockDim.x) {
+        const PackItem it = pack_item(item, N, K / 128);
+        uint32_t word[4][4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            q[(int64_t)(k0 + j) * N + n] = (uint8_t)((word >> (4 * nibble_of(j))) & 0xFu);
+        for (int i = 0; i < 4; ++i) {
+            const uint4 v = *(const uint4 *)(w + it.dst + 4 * i);
+            word[i][0] = v.x;
+            word[i][1] = v.y;
+            word[i][2] = v.z;
+            word[i][3] = v.w;
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            constexpr uint32_t m = 0x0F0F0F0Fu;
+            const uint32_t xy0 = __builtin_amdgcn_perm(word[1][t], word[0][t], 0x05010400u);
+            const uint32_t uv0 = __builtin_amdgcn_perm(word[1][t], word[0][t], 0x07030602u);
+            const uint32_t xy1 = __builtin_amdgcn_perm(word[3][t], word[2][t], 0x05010400u);
+            const uint32_t uv1 = __builtin_amdgcn_perm(word[3][t], word[2][t], 0x07030602u);
+            // xy: bytes x0 x1 y0 y1 of two columns; join the pairs
+            const uint32_t x = __builtin_amdgcn_perm(xy1, xy0, 0x05040100u), y = __builtin_amdgcn_perm(xy1, xy0, 0x07060302u);
+            const uint32_t u = __builtin_amdgcn_perm(uv1, uv0, 0x05040100u), v = __builtin_amdgcn_perm(uv1, uv0, 0x07060302u);
+            const uint32_t d[8] = {x & m, u & m, (x >> 4) & m, (u >> 4) & m, y & m, v & m, (y >> 4) & m, (v >> 4) & m};
+#pragma unroll
+            for (int j = 0; j < 8; ++j) __builtin_memcpy(q + it.src + (int64_t)(32 * t + j) * N, &d[j], 4);
+        }
     }
 }
 
@@ -198,8 +249,8 @@ hipError_t launch_pack(const uint8_t *q, const uint16_t *s, int K, int N, int G,
                        uint32_t *w_packed, uint16_t *s_packed, hipStream_t stream)
 {
     const int threads = 256;
-    const int64_t words = (int64_t)K * N / 8;
-    hipLaunchKernelGGL(pack_weights_kernel, dim3(blocks_for(words, threads)), dim3(threads), 0,
+    const int64_t items = (int64_t)K * N / 128;
+    hipLaunchKernelGGL(pack_weights_kernel, dim3(blocks_for(items, threads)), dim3(threads), 0,
                        stream, q, K, N, w_packed);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -212,8 +263,8 @@ hipError_t launch_unpack(const uint32_t *w_packed, const uint16_t *s_packed, int
                          int G, uint8_t *q, uint16_t *s, hipStream_t stream)
 {
     const int threads = 256;
-    const int64_t words = (int64_t)K * N / 8;
-    hipLaunchKernelGGL(unpack_weights_kernel, dim3(blocks_for(words, threads)), dim3(threads), 0,
+    const int64_t items = (int64_t)K * N / 128;
+    hipLaunchKernelGGL(unpack_weights_kernel, dim3(blocks_for(items, threads)), dim3(threads), 0,
                        stream, w_packed, K, N, q);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
