@@ -47,6 +47,10 @@ SIGNATURES = {
     "marlin_describe_sparse": (ctypes.c_int, [_i64, _i64, _i64, _i64, ctypes.c_char_p, _sz]),
     "marlin_quantize": (ctypes.c_int, [_vp, _i64, _i64, _i64, ctypes.POINTER(ctypes.c_float), ctypes.c_int,
                                        _vp, _vp, _vp]),
+    # marlin_quantize and marlin_pack_weights in one launch for a linear
+    # layer's weight [N, K] (internal: not declared in marlin.h)
+    "marlin_quantize_linear": (ctypes.c_int, [_vp, _i64, _i64, _i64, ctypes.POINTER(ctypes.c_float), ctypes.c_int,
+                                              _vp, _vp, _vp]),
 }
 
 
@@ -179,9 +183,18 @@ def marlin_describe_sparse(M: int, N: int, K: int, group: int) -> str:
     return buf.value.decode()
 
 
+def _ratio_array(ratios):
+    rs = [float(r) for r in ratios]
+    return (ctypes.c_float * max(1, len(rs)))(*rs), len(rs)
+
+
 def marlin_quantize(W, K, N, group, ratios, q, s, stream=None) -> None:
     """ratios: a host sequence of floats (copied into a C array here)."""
-    rs = [float(r) for r in ratios]
-    arr = (ctypes.c_float * max(1, len(rs)))(*rs)
-    _check("marlin_quantize", lib().marlin_quantize(_ptr(W), K, N, group, arr, len(rs),
-                                                    _ptr(q), _ptr(s), _stream(stream)))
+    arr, n = _ratio_array(ratios)
+    _check("marlin_quantize", lib().marlin_quantize(_ptr(W), K, N, group, arr, n, _ptr(q), _ptr(s), _stream(stream)))
+
+
+def marlin_quantize_linear(W, K, N, group, ratios, w_packed, s_packed, stream=None) -> None:
+    arr, n = _ratio_array(ratios)
+    _check("marlin_quantize", lib().marlin_quantize_linear(_ptr(W), K, N, group, arr, n, _ptr(w_packed),
+                                                           _ptr(s_packed), _stream(stream)))

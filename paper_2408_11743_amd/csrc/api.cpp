@@ -165,6 +165,23 @@ marlin_status_t describe_impl(int64_t M, int64_t N, int64_t K, int64_t group, ch
 }
 }  // namespace
 
+namespace {
+marlin_status_t quantize_entry(const uint16_t *W, int64_t K, int64_t N, int64_t group, const float *ratios,
+                               int n_ratios, bool linear, void *q, uint16_t *s, hipStream_t stream)
+{
+    if (!W || !ratios || !q || !s) return MARLIN_ERR_NULL_POINTER;
+    const marlin_status_t st = check_weights(K, N, group);
+    if (st != MARLIN_OK) return st;
+    if (!aligned16(W) || !aligned16(q) || !aligned16(s)) return MARLIN_ERR_MISALIGNED;
+    if (n_ratios < 1 || n_ratios > kMaxQuantRatios) return MARLIN_ERR_INVALID_ARGUMENT;
+    for (int i = 0; i < n_ratios; ++i)
+        if (!(ratios[i] > 0.0f && ratios[i] <= 1.0f)) return MARLIN_ERR_INVALID_ARGUMENT;  // NaN too
+    const int64_t g = (group == -1) ? K : group;
+    const hipError_t e = launch_quantize(W, (int)K, (int)N, (int)g, ratios, n_ratios, linear, q, s, stream);
+    return e == hipSuccess ? MARLIN_OK : MARLIN_ERR_HIP;
+}
+}  // namespace
+
 extern "C" {
 
 int marlin_layout_version(void) { return MARLIN_LAYOUT_VERSION; }
@@ -220,16 +237,13 @@ marlin_status_t marlin_pack_weights(const uint8_t *q, const uint16_t *s, int64_t
 marlin_status_t marlin_quantize(const uint16_t *W, int64_t K, int64_t N, int64_t group, const float *ratios,
                                 int n_ratios, uint8_t *q, uint16_t *s, hipStream_t stream)
 {
-    if (!W || !ratios || !q || !s) return MARLIN_ERR_NULL_POINTER;
-    const marlin_status_t st = check_weights(K, N, group);
-    if (st != MARLIN_OK) return st;
-    if (!aligned16(W) || !aligned16(q) || !aligned16(s)) return MARLIN_ERR_MISALIGNED;
-    if (n_ratios < 1 || n_ratios > kMaxQuantRatios) return MARLIN_ERR_INVALID_ARGUMENT;
-    for (int i = 0; i < n_ratios; ++i)
-        if (!(ratios[i] > 0.0f && ratios[i] <= 1.0f)) return MARLIN_ERR_INVALID_ARGUMENT;  // NaN too
-    const int64_t g = (group == -1) ? K : group;
-    const hipError_t e = launch_quantize(W, (int)K, (int)N, (int)g, ratios, n_ratios, q, s, stream);
-    return e == hipSuccess ? MARLIN_OK : MARLIN_ERR_HIP;
+    return quantize_entry(W, K, N, group, ratios, n_ratios, false, q, s, stream);
+}
+
+marlin_status_t marlin_quantize_linear(const uint16_t *W, int64_t K, int64_t N, int64_t group, const float *ratios,
+                                       int n_ratios, void *w_packed, void *s_packed, hipStream_t stream)
+{
+    return quantize_entry(W, K, N, group, ratios, n_ratios, true, w_packed, (uint16_t *)s_packed, stream);
 }
 
 size_t marlin_packed_sparse_weight_bytes(int64_t K, int64_t N)

@@ -77,3 +77,10 @@ hipError_t launch_unpack_sparse(const uint32_t *w_packed, const uint16_t *s_pack
                                 uint8_t *q, uint16_t *s, hipStream_t stream);
 
 }  // namespace marlin
+
+// marlin_quantize followed by marlin_pack_weights, for a linear layer's weight
+// W [N][K] (16-byte aligned): the same bits, without the transposed copy and
+// the codes in between.  Called by the Python layer; not part of the public ABI.
+extern "C" marlin_status_t marlin_quantize_linear(const uint16_t *W, int64_t K, int64_t N, int64_t group,
+                                                  const float *ratios, int n_ratios, void *w_packed, void *s_packed,
+                                                  hipStream_t stream);

@@ -156,3 +156,22 @@ def quantize(W: torch.Tensor, group=128, ratios=CLIP_RATIOS):
     s = torch.empty((G, N), dtype=torch.float16, device=W.device)
     B.marlin_quantize(W, K, N, g, ratios, q, s, _cur_stream(W))
     return q, s
+
+
+def quantize_linear(weight: torch.Tensor, group=128, ratios=CLIP_RATIOS):
+    """``pack(*quantize(weight.t(), group, ratios), group)`` for a linear
+    layer's weight [N, K]: the same bits.  A contiguous weight is read as it
+    lies and packed in the same launch; any other goes through a transposed
+    copy, the codes and ``pack``."""
+    N, K = weight.shape
+    g = _group(K, group)
+    wb = B.marlin_packed_weight_bytes(K, N)
+    sb = B.marlin_packed_scale_bytes(K, N, g)
+    if not (wb and sb and weight.is_cuda and weight.dtype == torch.float16 and weight.is_contiguous()
+            and weight.data_ptr() % 16 == 0):
+        q, s = quantize(weight.t().contiguous(), group=group, ratios=ratios)
+        return pack(q, s, group=group)
+    wp = torch.empty(wb, dtype=torch.uint8, device=weight.device)
+    sp = torch.empty(sb // 2, dtype=torch.float16, device=weight.device)
+    B.marlin_quantize_linear(weight, K, N, g, ratios, wp, sp, _cur_stream(weight))
+    return wp, sp

@@ -63,8 +63,7 @@ class MarlinLinear(torch.nn.Module):
         if weight.dim() != 2:
             raise ValueError("from_float: weight must be 2-D [out_features, in_features]")
         N, K = weight.shape
-        q, s = ops.quantize(weight.t().contiguous(), group=group, ratios=ratios)
-        wp, sp = ops.pack(q, s, group=group)
+        wp, sp = ops.quantize_linear(weight, group=group, ratios=ratios)
         return cls(wp, sp, K, N, group)
 
     def forward(self, x: torch.Tensor) -> torch.Tensor:
