@@ -88,11 +88,19 @@ class Workspace:
 _default_ws: dict = {}
 
 
+def _packed_bytes(K: int, N: int, g: int, sparse: bool):
+    """marlin_packed_(sparse_)weight_bytes and marlin_packed_scale_bytes, as
+    arithmetic: a call into the library costs as much as the rest of a check."""
+    if (K < 128 or N < 64 or K % 128 or N % 64 or K > 1 << 20 or N > 1 << 20 or K * N >= 1 << 32
+            or (g != -1 and g != K and (g <= 0 or g % 128 or K % g))):
+        return 0, 0
+    return (K * N // 8 * 3 if sparse else K * N // 2), 2 * N * (1 if g == -1 else K // g)
+
+
 def _check_packed(func: str, wp: torch.Tensor, sp: torch.Tensor, K: int, N: int, g: int, sparse: bool) -> None:
     """Packed weights and scales: device tensors of the byte counts K, N and
     the group imply (a wrong size would make the kernels read past them)."""
-    wb = B.marlin_packed_sparse_weight_bytes(K, N) if sparse else B.marlin_packed_weight_bytes(K, N)
-    sb = B.marlin_packed_scale_bytes(K, N, g)
+    wb, sb = _packed_bytes(K, N, g, sparse)
     if wb == 0 or sb == 0:
         raise B.MarlinError(func, 2)
     if not (wp.is_cuda and sp.is_cuda):
@@ -126,13 +134,28 @@ def gemm(A: torch.Tensor, wp: torch.Tensor, sp: torch.Tensor, K: int, N: int, gr
     elif (tuple(out.shape) != (M, N) or out.dtype != torch.float16 or out.device != A.device
           or not out.is_contiguous()):
         raise ValueError("gemm: out must be a contiguous float16 [%d, %d] tensor on %s" % (M, N, A.device))
-    need = B.marlin_workspace_bytes(M, N, K, g)
+    # Host time per call is what a small decode step waits for: one call into
+    # the library, which checks the workspace itself (its status says when to
+    # grow it, before anything is enqueued), and one workspace per (device,
+    # stream), made once.  4096 x 4096 at M = 1, back to back: 18 us a call with
+    # three size queries and a throw-away workspace, 8.1 us now (5 us of GPU
+    # time).
+    index = A.device.index
+    stream = torch._C._cuda_getCurrentRawStream(index)
     if workspace is None:
-        key = (A.device, torch.cuda.current_stream(A.device).cuda_stream)
-        workspace = _default_ws.setdefault(key, Workspace(A.device))
-    buf = workspace.ensure(need)
-    fn = B.marlin_gemm_sparse if sparse else B.marlin_gemm
-    fn(A, wp, sp, out, buf, buf.numel(), M, N, K, g, _cur_stream(A))
+        workspace = _default_ws.get((index, stream))
+        if workspace is None:
+            workspace = _default_ws.setdefault((index, stream), Workspace(A.device))
+    handle = B.lib()
+    fn = handle.marlin_gemm_sparse if sparse else handle.marlin_gemm
+    buf = workspace.buf
+    args = A.data_ptr(), wp.data_ptr(), sp.data_ptr(), out.data_ptr()
+    status = fn(*args, buf.data_ptr(), buf.numel(), M, N, K, g, stream)
+    if status == 5:  # WORKSPACE_TOO_SMALL
+        buf = workspace.ensure(B.marlin_workspace_bytes(M, N, K, g))
+        status = fn(*args, buf.data_ptr(), buf.numel(), M, N, K, g, stream)
+    if status:
+        raise B.MarlinError("marlin_gemm_sparse" if sparse else "marlin_gemm", status)
     return out
 
 
