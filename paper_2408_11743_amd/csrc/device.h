@@ -318,6 +318,20 @@ __device__ __forceinline__ void combine_tiles(const GemmProblem &p, int *flags, 
     if (reduce_first) reduce(c_first, false);
 }
 
+// Two adjacent 16-column blocks of 16 rows, as the MFMAs leave them (lane l: row
+// l % 16, columns 4 (l / 16) .. + 3 of each block), to 16 bytes per lane: odd
+// 16-lane rows of the first block change places with even ones of the second,
+// so that lane l holds columns 8 (l / 32) .. + 7 of block (l / 16) % 2.  A
+// store then covers 64 bytes of a row instead of 32.
+__device__ __forceinline__ u32x4_t join_blocks(half4_t b0, half4_t b1)
+{
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    const u32x2_t x = __builtin_bit_cast(u32x2_t, b0), y = __builtin_bit_cast(u32x2_t, b1);
+    const auto lo = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
+    return u32x4_t{lo[0], hi[0], lo[1], hi[1]};
+}
+
 // ---- 16-byte partial slots, combined wave by wave ----
 // The kernels with large tiles (16 blocks per wave, 64 or 128 KiB per slot)
 // keep a block as 64 float4, lane by lane (block at float4 index blk*64), and

@@ -283,23 +283,28 @@ __global__ void __launch_bounds__(64 * WN * WM, 1) w4a16_tile_kernel(GemmProblem
         const int r0 = row0_of(c) + wm * 16 * MBW, rows = rows_of(c) - wm * 16 * MBW;
         const uint32_t nb0 = (cg_of(c) * WN + (uint32_t)wn) * NBW;  // first 16-column block
         if ((nb0 >> 2) >= n_tiles) return;
+        half4_t cs[NBW] = {};
+        if constexpr (PER_CHANNEL) {
 #pragma unroll
-        for (int b = 0; b < NBW; ++b) {
-            half4_t cs = {};
-            if constexpr (PER_CHANNEL)
-                cs = *(const half4_t *)(p.S + (int64_t)((nb0 + b) >> 2) * 64 + lg * 16 + ((nb0 + b) & 3u) * 4);
+            for (int b = 0; b < NBW; ++b)
+                cs[b] = *(const half4_t *)(p.S + (int64_t)((nb0 + b) >> 2) * 64 + lg * 16 + ((nb0 + b) & 3u) * 4);
+        }
+        auto rounded = [&](int b, int mb) -> half4_t {
+            float4_t v = out[b * MBW + mb];
+            if constexpr (PER_CHANNEL) {
 #pragma unroll
-            for (int mb = 0; mb < MBW; ++mb) {
-                const int m = mb * 16 + (lane & 15);
-                if (m < rows) {
-                    float4_t vv = out[b * MBW + mb];
-                    if constexpr (PER_CHANNEL) {
+                for (int i = 0; i < 4; ++i) v[i] *= (float)cs[b][i];
+            }
+            return half4_t{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+        };
+        uint16_t *const at = p.C + (int64_t)(nb0 * 16 + (lg & 1) * 16 + (lg >> 1) * 8);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) vv[i] *= (float)cs[i];
-                    }
-                    const half4_t h = {(_Float16)vv[0], (_Float16)vv[1], (_Float16)vv[2], (_Float16)vv[3]};
-                    *(half4_t *)(p.C + (int64_t)(r0 + m) * p.N + (nb0 + b) * 16 + lg * 4) = h;
-                }
+        for (int mb = 0; mb < MBW; ++mb) {
+            const int m = mb * 16 + (lane & 15);
+#pragma unroll
+            for (int b = 0; b < NBW; b += 2) {
+                const u32x4_t h = join_blocks(rounded(b, mb), rounded(b + 1, mb));
+                if (m < rows) *(u32x4_t *)(at + (int64_t)(r0 + m) * p.N + b * 16) = h;
             }
         }
     };
