@@ -24,8 +24,7 @@ struct GemmProblem {
     int K;
     int G;                // scale rows
     int KU;               // 128-row blocks of K
-    int units;            // column tiles * KU: 128-row blocks of all (with tiles beyond them: the shared) column tiles
-    int tiles;            // eight-wave tile and wide kernels: all tiles; those past units / KU are whole
+    int units;            // column tiles * KU: 128-row blocks of all column tiles (eight-wave kernels: of the shared ones)
     int gran;             // units per partition item: KU (whole tiles) or 1
     int per_wg;           // (units / gran) / grid
     int extra;            // (units / gran) % grid
@@ -33,6 +32,7 @@ struct GemmProblem {
     uint32_t gmagic;      // ceil(2^26 / group_units): row of block ku = (ku * 2^6 * gmagic) >> 32
     uint32_t grid_magic;  // ceil(2^32 / grid) (0 for grid 1): w * extra / grid = mulhi(w * extra, grid_magic)
     uint32_t ku_magic;    // ceil(2^32 / KU) where u / KU = mulhi(u, ku_magic) for every unit u, else 0
+    int tiles;            // eight-wave tile and wide kernels: all tiles; those past units / KU are whole
 };
 
 // Device facts cached per device.
