@@ -1,364 +1,453 @@
 // W4A16 GEMM for gfx950 with 64-row groups and two waves per SIMD:
 // C[M,N] = A[M,K] * (s * (q - 8)), fp32 accumulation.
 //
-// The tiles, units, partition and combination are the stream kernel's with
-// four 16-row blocks (64 rows x 128 columns per tile, gemm.hip); the work of
-// a stage is split differently.  Eight waves form four pairs; pair k takes
-// 128-row block k of the stage (the waves of a work-group split K in four),
-// and the two waves of a pair take one packed 64-column tile each, 64 x 64
-// outputs per wave.  A pair shares its block's 64 activation rows: each wave
-// brings half of them into the pair's LDS ring slot by direct-to-LDS loads,
-// and the pair meets at a barrier before reading them and again before the
-// slot is refilled.  Waves w and w + 4 run on one SIMD, so one wave's code
-// conversion overlaps the other's MFMAs (with one wave per SIMD the two run
-// in turn).  Codes are converted with the magic number (exact q - 8) and the
+// The tiles, units and ranges are the stream kernel's with four 16-row blocks
+// (64 rows x 128 columns per tile, gemm.hip).  Eight waves: four along N take 32
+// columns each, and pairs of waves (w and w + 4) split K, one 128-row block each
+// per stage; the pair's sums meet in LDS when a tile segment ends (Algorithm 1's
+// reduction).  Codes are converted with the magic number (exact q - 8) and the
 // group scale multiplies the fp16 weights (Section 3.4, "Dequantization and
-// Tensor Cores", "Groups and Instruction Ordering"); the four waves of a
-// column half meet in LDS when a tile segment ends (Algorithm 1's
-// reduction over the waves that share an output tile).
+// Tensor Cores", "Groups and Instruction Ordering").
+//
+// Everything a stage needs arrives by direct-to-LDS loads in a ring of three
+// 50 KiB slots: two blocks' 64 activation rows (XOR-swizzled), each wave's words
+// and scale row.  One barrier per stage, between a wave's second and third
+// k-step: by then it holds the rest of the stage in registers, so the slot is
+// free, and the next stage has landed.  The next stage's first rows, words and
+// scales are read during the last two k-steps and its last rows during the
+// first two, and the refill's loads are spread over those: with the loads in
+// one burst per stage and two barriers around the operand reads the matrix cores
+// idled at every stage.  Reads in flight never cross the loop's back edge or a
+// branch: the compiler takes their registers as written and could move them.
+//
+// Bound: LDS bandwidth and vector issue (193 KiB of LDS traffic and 3.25 vector
+// instructions per MFMA in a stage).  8192 x 28672 at M = 64 44.5 us (before
+// 46.5); without the conversion 36.0, without the loads 36.6, without both 26.1;
+// 4096 x 11008 at M = 128 21.2 us (24.2), 1792 x 14592 at M = 114 13.2 (15.3).
 #include <hip/hip_runtime.h>
 #include <stdio.h>
 
 #include "device.h"
 #include "internal.h"
 
-namespace marlin {
-namespace {
+namespace {  // outside marlin: the kernel's name is what marlin_describe prints
 
-using namespace dev;
+using namespace marlin;
+using namespace marlin::dev;
 
-// Eight fp16 weights times one scale (in both halves of s2), one rounding each.
-__device__ __forceinline__ half8_t scale_weights(half8_t w, half2_t s2)
+constexpr int kPairP = 3;                      // ring slots
+constexpr int kPairA = 64 * 256;               // a block's 64 rows x 128 k, bytes
+constexpr int kPairWAt = 2 * kPairA;           // then the waves' words (2 KiB each)
+constexpr int kPairSAt = kPairWAt + 8 * 2048;  // and scale rows (256 B each)
+constexpr int kPairStage = kPairSAt + 8 * 256;
+static_assert(kPairP * kPairStage <= 160 * 1024 - 64, "LDS");
+
+// One quarter (codes 2q and 2q + 1) of a word: q - 8 exactly by the magic
+// number, times the scale (SCALED, one rounding).
+template <bool SCALED>
+__device__ __forceinline__ half2_t pair_quarter(uint32_t x, int q, half2_t s2, const DequantConsts &k)
 {
-    const u32x4_t u = __builtin_bit_cast(u32x4_t, w);
-    return __builtin_bit_cast(half8_t, u32x4_t{as_u32(as_h2(u[0]) * s2), as_u32(as_h2(u[1]) * s2),
-                                               as_u32(as_h2(u[2]) * s2), as_u32(as_h2(u[3]) * s2)});
+    const half2_t sub = {(_Float16)1032.0f, (_Float16)1032.0f};
+    const half2_t mul = {(_Float16)0.0625f, (_Float16)0.0625f};
+    const half2_t add = {(_Float16)-72.0f, (_Float16)-72.0f};
+    const uint32_t y = (q >> 1) ? x >> 8 : x;
+    const half2_t r = (q & 1) == 0 ? as_h2((y & k.lo) | k.ex) - sub
+                                   : __builtin_elementwise_fma(as_h2((y & k.hi) | k.ex), mul, add);
+    return SCALED ? r * s2 : r;
 }
 
 template <bool PER_CHANNEL>
 __global__ void __launch_bounds__(512, 1) w4a16_pair_kernel(GemmProblem p)
 {
-    constexpr int KS = 4;               // 128-row blocks of K per stage (one per pair)
-    constexpr int D = 2;                // ring depth
-    constexpr int MB = 4;               // 16-row blocks per wave (all 64 rows)
-    constexpr int NBW = 4;              // 16-column blocks per wave (one packed tile)
-    constexpr int kOwn = 4;             // blocks a wave holds after the reduction
-    constexpr int kAStage = 64 * 256;   // one block's 64 rows x 128 k, bytes
-    constexpr int kADma = 8;            // this wave's half of the block's 16 one-KiB loads
-    constexpr int kWL = NBW;            // weight loads per stage
-    constexpr int kSL = PER_CHANNEL ? 0 : 2;
-    constexpr int kLoads = kADma + kWL + kSL;
-    static_assert((D - 1) * kLoads + kWL + kSL < 64, "vmcnt range");
-    __shared__ __attribute__((aligned(16))) uint8_t a_lds[KS * D * kAStage];  // 128 KiB
-    __shared__ int flags[2];
+    constexpr int P = kPairP, kStage = kPairStage;
+    constexpr int KS = 2;    // 128-row blocks of K per stage
+    constexpr int MB = 4;    // 16-row blocks per wave
+    constexpr int NB = 2;    // 16-column blocks per wave
+    constexpr int kOwn = NB * MB / 2;  // blocks a wave keeps after the reduction
+    constexpr int kDmaA = 4, kDmaW = 2, kDmaS = PER_CHANNEL ? 0 : 1;
+    constexpr int kLoads = kDmaA + kDmaW + kDmaS;
+    __shared__ __attribute__((aligned(16))) uint8_t ring[P * kStage];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int ks = wave & 3;    // the pair: 128-row block of the stage
-    const int hf = wave >> 2;   // packed 64-column tile of the column tile (column half)
+    const int wn = wave & 3, kg = wave >> 2;  // 32-column part, block of the stage
     const int lg = lane >> 4;
+    const DequantConsts dq = dequant_consts();
     const int KU = p.KU;
     const int grid = gridDim.x;
     const int wg = xcd_local_wg(blockIdx.x, grid);
     const int u0 = range_start(p, wg, grid);
     const int u1 = range_start(p, wg + 1, grid);
-    const int c_first = tile_of(p, u0);
-    const int c_last = tile_of(p, u1 - 1);
-    const int k0 = u0 - c_first * KU;
-    const int k1 = u1 - c_last * KU;
+    const int c_begin = tile_of(p, u0);
+    const int c_end = tile_of(p, u1 - 1);  // the range's last tile
+    const int k0 = u0 - c_begin * KU;
+    const int k1 = u1 - c_end * KU;
+    const int n_st = c_begin == c_end ? (k1 - k0 + KS - 1) / KS
+                                      : (KU - k0 + KS - 1) / KS + (c_end - c_begin - 1) * ((KU + KS - 1) / KS) +
+                                            (k1 + KS - 1) / KS;
+    auto end_of = [&](int c) { return c == c_end ? k1 : c < c_end ? KU : 0; };
 
-    // Tile c: column tile c / rg (128 columns, packed tiles 2 (c / rg) and
-    // 2 (c / rg) + 1), row group c % rg (64 rows).
+    // Tile c: column tile c / rg (128 columns), row group c % rg (64 rows).
     const uint32_t RG = (uint32_t)p.rg;
     auto col_of = [&](int c) -> uint32_t { return RG == 1 ? (uint32_t)c : (uint32_t)c / RG; };
-    auto ptile_of = [&](int c) -> uint32_t { return col_of(c) * 2u + (uint32_t)hf; };
-    auto w_tile = [&](int c) -> uint32_t { return ptile_of(c) * (uint32_t)KU * 4096u; };
-    auto s_tile = [&](int c) -> uint32_t { return (ptile_of(c) * (uint32_t)p.G) << 7; };
     auto row0_of = [&](int c) -> int { return RG == 1 ? 0 : (int)((uint32_t)c - col_of(c) * RG) * 64; };
     auto rows_of = [&](int c) -> int {
         const int r = p.M - row0_of(c);
         return r < 64 ? r : 64;
     };
+    // this wave's packed 64-column tile, and its half of it
+    auto ptile_of = [&](int c) -> uint32_t { return col_of(c) * 2u + (uint32_t)(wn >> 1); };
 
-    const uint32_t w_lane = (uint32_t)ks * 4096u + (uint32_t)lane * 16u;
-    // Scale runs: lane group g of the packed 128-byte row holds, for each
-    // 16-column block, the scales of columns 4g .. 4g + 3; the weight operand's
-    // column is lane % 16, so a lane loads run (lane % 16) / 4 and keeps
-    // element lane % 4 of it (one v_perm per block).
-    const uint32_t s_lane = (uint32_t)((lane & 15) >> 2) * 32u;
-    const uint32_t s_sel = 0x01000100u + (uint32_t)(lane & 3) * 0x02020202u;
-    // Direct-to-LDS loads: load i of the block (0..15) brings rows 4i .. 4i + 3,
-    // lane l row 4i + l/16, 16-byte chunk (l % 16) ^ row (XOR swizzle); this
-    // wave issues loads 8 hf .. 8 hf + 7, and loads q, q + 4 are 16 rows
-    // apart with the same swizzle.
-    uint32_t a_dma[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int r = 4 * (8 * hf + q) + lg;
-        a_dma[q] = (uint32_t)(r * p.K + (((lane & 15) ^ (r & 15)) * 8)) * 2u + (uint32_t)ks * 256u;
-    }
+    // ---- per-lane address parts ----
+    // A: load i of this wave brings rows 4 wn + lg + 16 i of its block (all
+    // with one swizzle)
+    const uint32_t a_dma = (uint32_t)((4 * wn + lg) * p.K + (((lane & 15) ^ ((4 * wn + lg) & 15)) * 8)) * 2u;
     const uint32_t a_rows16 = (uint32_t)p.K * 32u;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)a_lds;
-    const uint32_t lds_pair = lds0 + (uint32_t)(ks * D * kAStage);  // the pair's ring
-    // Operand reads, k-step t: row mb*16 + l%16, chunk (4t + l/16) ^ (l%16);
-    // the slot and the row block are instruction offsets.
-    uint32_t a_rd[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-        a_rd[t] = lds_pair + (uint32_t)((lane & 15) * 256) + (uint32_t)(((4 * t + lg) ^ (lane & 15)) << 4);
+    const uint32_t w_lane = (uint32_t)lane * 16u + (uint32_t)(wn & 1) * 2048u;
+    const uint32_t s_lane = (uint32_t)(lane & 31) * 4u;
     const uint32_t w_bytes = (uint32_t)p.K * (uint32_t)(p.N / 2);
     const uint32_t s_bytes = (uint32_t)p.G * (uint32_t)p.N * 2u;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)ring;
+    // Operand reads, k-step t: row l % 16 of a 16-row block, chunk (4t + l / 16)
+    // ^ (l % 16).  A wave's row block mb is row block (mb + 2 kg) % 4 of the
+    // tile, so that the blocks it keeps after the reduction are its first two.
+    uint32_t a_rd[4][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const uint32_t at = lds0 + (uint32_t)(kg * kPairA + (lane & 15) * 256) +
+                            (uint32_t)(((4 * t + lg) ^ (lane & 15)) << 4);
+        a_rd[t][0] = at + (uint32_t)kg * 8192u;
+        a_rd[t][1] = at + (uint32_t)(1 - kg) * 8192u;
+    }
+    const uint32_t w_rd = lds0 + (uint32_t)(kPairWAt + wave * 2048 + lane * 16);
+    // this lane's column scale of block b: byte (cn / 4) * 32 + (nb * 4 + cn % 4) * 2, cn = lane % 16
+    const uint32_t s_rd =
+        lds0 + (uint32_t)(kPairSAt + wave * 256 + ((lane & 15) >> 2) * 32 + (wn & 1) * 16 + (lane & 3) * 2);
 
-    u32x4_t wr[D][NBW];
-    half8_t sr[D][2];
-
-    // ---- load cursor (work-group uniform) ----
-    int ld_c = c_first, ld_ku = k0;
-    int ld_end = (c_first == c_last) ? k1 : KU;
-    uint32_t ld_w = w_tile(ld_c) + (uint32_t)ld_ku * 4096u;
-    uint32_t ld_s = s_tile(ld_c);
-    const uint16_t *ld_a = p.A + (int64_t)row0_of(ld_c) * p.K;
-    uint32_t a_bytes = (uint32_t)rows_of(ld_c) * (uint32_t)p.K * 2u;
-
-    auto issue = [&](int j) {
-        const int my = ld_ku + ks;
+    // ---- load cursor ----
+    int ld_c = c_begin, ld_ku = k0;
+    int ld_end = end_of(ld_c);
+    uint32_t ld_slot = 0;
+    uint32_t ld_w, ld_s, a_bytes;
+    const uint16_t *ld_a;
+    auto ld_tile = [&]() {
+        const int c = ld_end > 0 ? ld_c : c_end;
+        ld_w = ptile_of(c) * (uint32_t)KU << 12;
+        ld_s = ptile_of(c) * (uint32_t)p.G << 7;
+        ld_a = p.A + (int64_t)row0_of(c) * p.K;
+        a_bytes = (uint32_t)rows_of(c) * (uint32_t)p.K * 2u;
+    };
+    ld_tile();
+    // Load i of a stage (0 .. kLoads - 1), all direct to LDS; a block past the
+    // segment loads zeros through an empty descriptor.
+    auto issue = [&](int i) {
+        const int my = ld_ku + kg;
         const bool on = my < ld_end;
-        {  // first, so a stage's LDS rows are its oldest loads
-            const __amdgpu_buffer_rsrc_t rd =
+        uint32_t slot = lds0 + ld_slot;
+        asm volatile("" : "+s"(slot));
+        if (i < kDmaA) {
+            const __amdgpu_buffer_rsrc_t ra =
                 __builtin_amdgcn_make_buffer_rsrc((void *)ld_a, (short)0, on ? a_bytes : 0u, kBufferFlags);
-            uint32_t slot = lds_pair;
-            asm volatile("" : "+s"(slot));
-            slot += (uint32_t)(j * kAStage + hf * 8192);
-            uint32_t dma[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                dma[q] = a_dma[q];
-                asm volatile("" : "+v"(dma[q]));  // formed per stage, not held
-            }
-#pragma unroll
-            for (int q = 0; q < kADma; ++q)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    rd, (__attribute__((address_space(3))) void *)(uintptr_t)(slot + (uint32_t)(q * 1024)), 16,
-                    (int)(dma[q & 3] + (uint32_t)(q >> 2) * a_rows16), ld_ku * 256, 0, 0);
-        }
-        issue_order_point();
-        const __amdgpu_buffer_rsrc_t rw =
-            __builtin_amdgcn_make_buffer_rsrc((void *)p.W, (short)0, on ? w_bytes : 0u, kBufferFlags);
-#pragma unroll
-        for (int b = 0; b < NBW; ++b)
-            wr[j][b] = __builtin_bit_cast(
-                u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rw, w_lane + b * 1024, ld_w, kAuxNonTemporal));
-        if constexpr (!PER_CHANNEL) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                ra,
+                (__attribute__((address_space(3))) void *)(uintptr_t)(slot + (uint32_t)(kg * kPairA + wn * 1024 + i * 4096)),
+                16, (int)(a_dma + (uint32_t)i * a_rows16), my * 256, 0, 0);
+        } else if (i < kDmaA + kDmaW) {
+            const __amdgpu_buffer_rsrc_t rw =
+                __builtin_amdgcn_make_buffer_rsrc((void *)p.W, (short)0, on ? w_bytes : 0u, kBufferFlags);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rw,
+                (__attribute__((address_space(3))) void *)(uintptr_t)(
+                    slot + (uint32_t)(kPairWAt + wave * 2048 + (i - kDmaA) * 1024)),
+                16, (int)(w_lane + (uint32_t)(i - kDmaA) * 1024u), (int)(ld_w + ((uint32_t)my << 12)), 0,
+                kAuxNonTemporal);
+        } else if (i < kLoads) {
             const __amdgpu_buffer_rsrc_t rs =
                 __builtin_amdgcn_make_buffer_rsrc((void *)p.S, (short)0, on ? s_bytes : 0u, kBufferFlags);
-            const uint32_t s_off = ld_s + ((uint32_t)scale_row_of(my, p) << 7);
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-                sr[j][i] = __builtin_bit_cast(half8_t, __builtin_amdgcn_raw_buffer_load_b128(rs, s_lane + i * 16,
-                                                                                             s_off, 0));
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs, (__attribute__((address_space(3))) void *)(uintptr_t)(slot + (uint32_t)(kPairSAt + wave * 256)), 4,
+                (int)s_lane, (int)(ld_s + ((uint32_t)scale_row_of(my, p) << 7)), 0, 0);
         }
-        issue_order_point();  // stages do not interleave
+        issue_order_point();
     };
     auto advance_ld = [&]() {
+        ld_slot = ld_slot == (uint32_t)((P - 1) * kStage) ? 0u : ld_slot + (uint32_t)kStage;
         ld_ku += KS;
-        ld_w += KS * 4096u;
-        if (ld_ku >= ld_end) {  // next segment
+        if (ld_ku >= ld_end) {
             ld_c += 1;
             ld_ku = 0;
-            ld_end = (ld_c < c_last) ? KU : (ld_c == c_last) ? k1 : 0;
-            ld_w = w_tile(ld_c);
-            ld_s = s_tile(ld_c);
-            if (RG > 1 && ld_end > 0) {
-                ld_a = p.A + (int64_t)row0_of(ld_c) * p.K;
-                a_bytes = (uint32_t)rows_of(ld_c) * (uint32_t)p.K * 2u;
-            }
+            ld_end = end_of(ld_c);
+            ld_tile();
         }
     };
-
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-        issue(j);
+    for (int j = 0; j < P; ++j) {
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) issue(i);
         advance_ld();
     }
 
-    const int n_st = (c_first == c_last)
-                         ? (k1 - k0 + KS - 1) / KS
-                         : (KU - k0 + KS - 1) / KS + (c_last - c_first - 1) * ((KU + KS - 1) / KS) +
-                               (k1 + KS - 1) / KS;
-
-    float4_t acc[NBW][MB];
-#pragma unroll
-    for (int b = 0; b < NBW; ++b)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) acc[b][mb] = float4_t{0.f, 0.f, 0.f, 0.f};
+    float4_t acc[NB][MB];
     const float4_t zero4 = {0.f, 0.f, 0.f, 0.f};
-    const DequantConsts dq = dequant_consts();
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[b][mb] = zero4;
 
-    // One stage (ring slot j, `later` stages issued after it).  Every wave
-    // passes both barriers, also one whose block lies past the segment.
-    auto compute = [&](int j, int later, bool active) {
-        // this wave's rows of the stage have landed (the loads issued after
-        // them are the stage's weight and scale loads and `later` stages);
-        // the barrier waits for the partner's
-        wait_vmcnt_n(later * kLoads + kWL + kSL);
-        __builtin_amdgcn_s_barrier();
-        u32x4_t v[4 * MB];
-        if (active) {
+    u32x4_t av[4][MB];        // [k-step][row block]
+    u32x4_t wv[NB], wn_[NB];  // packed words, k-step in the element: this stage's, the next one's
+    uint32_t sv[NB];          // column scales as read
+    half2_t s2[NB];
+    half2_t nx[4];            // converted operand of the next four MFMAs
+    uint32_t rd_slot = 0;
+    auto read_a = [&](int t, int mb) {
+        asm volatile("ds_read_b128 %0, %1 offset:%2"
+                     : "=v"(av[t][mb])
+                     : "v"(a_rd[t][mb >> 1] + rd_slot), "i"((mb & 1) * 4096));
+    };
+    auto read_w = [&](int b) {
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(wn_[b]) : "v"(w_rd + rd_slot), "i"(b * 1024));
+    };
+    auto read_s = [&](int b) {
+        asm volatile("ds_read_u16 %0, %1 offset:%2" : "=v"(sv[b]) : "v"(s_rd + rd_slot), "i"(b * 8));
+    };
+    auto landed_a = [&](int t) {
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+        for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(av[t][mb]));
+    };
+    auto landed_ws = [&]() {
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    asm volatile("ds_read_b128 %0, %1 offset:%2"
-                                 : "=v"(v[mb * 4 + t])
-                                 : "v"(a_rd[t]), "i"(j * kAStage + mb * 4096));
-            asm volatile("s_waitcnt lgkmcnt(0)"
-                         : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]),
-                           "+v"(v[7]), "+v"(v[8]), "+v"(v[9]), "+v"(v[10]), "+v"(v[11]), "+v"(v[12]),
-                           "+v"(v[13]), "+v"(v[14]), "+v"(v[15])::"memory");
-        }
-        // both waves of the pair have their rows: the slot may be refilled
-        __builtin_amdgcn_s_barrier();
-        if (!active) return;
-        half2_t s2[NBW];
-        if constexpr (!PER_CHANNEL) {
-#pragma unroll
-            for (int b = 0; b < NBW; ++b) {
-                const u32x4_t u = __builtin_bit_cast(u32x4_t, sr[j][b >> 1]);
-                s2[b] = as_h2(__builtin_amdgcn_perm(u[2 * (b & 1) + 1], u[2 * (b & 1)], s_sel));
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-#pragma unroll
-            for (int b = 0; b < NBW; ++b) {
-                half8_t w = dequant_magic(wr[j][b][t], dq);
-                if constexpr (!PER_CHANNEL) w = scale_weights(w, s2[b]);
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-                    acc[b][mb] = mfma(w, __builtin_bit_cast(half8_t, v[mb * 4 + t]), acc[b][mb]);
+        for (int b = 0; b < NB; ++b) {
+            asm volatile("" : "+v"(wn_[b]));
+            if constexpr (!PER_CHANNEL) {
+                asm volatile("" : "+v"(sv[b]));
+                s2[b] = as_h2(sv[b] | (sv[b] << 16));
             }
         }
     };
+    // MFMA of k-step t, column block b and row block mb, with one quarter of
+    // the next operand's conversion
+    auto slot = [&](int t, int b, int mb, half8_t w, uint32_t next, half2_t ns) {
+        acc[b][mb] = mfma(w, __builtin_bit_cast(half8_t, av[t][mb]), acc[b][mb]);
+        nx[mb] = pair_quarter<!PER_CHANNEL>(next, mb, ns, dq);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto operand = [&]() {
+        return half8_t{nx[0].x, nx[0].y, nx[1].x, nx[1].y, nx[2].x, nx[2].y, nx[3].x, nx[3].y};
+    };
 
-    // After the reduction wave (ks, hf) holds row block ks of the column
-    // blocks of its half hf: tile block (4 hf + j) * MB + ks for j = 0..3.
-    auto own = [&](int j) { return (4 * hf + j) * MB + ks; };
+    // block j of this wave after the reduction = column block j / 2, row block 2 kg + j % 2
+    auto own = [&](int j) { return wave * kOwn + j; };
     auto store_c = [&](int c, const float4_t *out) {
-        const int r0 = row0_of(c), rows = rows_of(c);
-        const int col = (int)col_of(c);
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));  // addresses formed here, not held across the loop
+        const int lg = lane >> 4;
+        const int r0 = row0_of(c) + kg * 32, rows = rows_of(c) - kg * 32;
+        const uint32_t pt = ptile_of(c);
+        half4_t cs[NB] = {};
+        if constexpr (PER_CHANNEL) {
 #pragma unroll
-        for (int j = 0; j < kOwn; ++j) {
-            const int blk = own(j);
-            const int b = blk / MB, mb = blk % MB;
-            const int m = mb * 16 + (lane & 15);
-            if (m < rows) {
-                const int nbg = col * 8 + b;
-                float4_t v = out[j];
-                if constexpr (PER_CHANNEL) {
-                    const half4_t s4 = *(const half4_t *)(p.S + (int64_t)(nbg >> 2) * 64 + lg * 16 + (nbg & 3) * 4);
+            for (int b = 0; b < NB; ++b)
+                cs[b] = *(const half4_t *)(p.S + (int64_t)pt * 64 + lg * 16 + ((wn & 1) * 2 + b) * 4);
+        }
+        auto rounded = [&](int b, int mb) -> half4_t {
+            float4_t v = out[b * 2 + mb];
+            if constexpr (PER_CHANNEL) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] *= (float)s4[i];
-                }
-                const half4_t h = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
-                *(half4_t *)(p.C + (int64_t)(r0 + m) * p.N + nbg * 16 + lg * 4) = h;
+                for (int i = 0; i < 4; ++i) v[i] *= (float)cs[b][i];
             }
+            return half4_t{(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+        };
+        uint16_t *const at = p.C + (int64_t)(pt * 64 + (wn & 1) * 32 + (lg & 1) * 16 + (lg >> 1) * 8);
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb) {
+            const int m = mb * 16 + (lane & 15);
+            const u32x4_t h = join_blocks(rounded(0, mb), rounded(1, mb));
+            if (m < rows) *(u32x4_t *)(at + (int64_t)(r0 + m) * p.N) = h;
         }
     };
-
-    constexpr int kSlotFloats = 2 * NBW * MB * 256;  // the tile's 32 blocks
+    constexpr int kSlotFloats = 8 * kOwn * 256;
     float *const my_slots = p.partials + (int64_t)wg * 2 * kSlotFloats;
-    bool has_first = false, has_last = false;
-    float4_t last_out[kOwn];
+    bool reduce_first = false;  // this wave sums the range's first tile at the end
+    int cp_c = c_begin, cp_ku = k0, cp_begin = k0;
+    int cp_end = end_of(cp_c);
+    // Sum the two blocks' tiles: wave (wn, kg) keeps row blocks 2 kg and 2 kg + 1
+    // and gives the others to its partner, through ring slot `at` (free: every
+    // wave holds its stage's operands in registers, and the slot's refill is
+    // issued after this).
+    auto reduce_halves = [&](uint32_t at) {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        float4_t *const mine = reinterpret_cast<float4_t *>(ring + at + (uint32_t)wave * 4096u);
+        const float4_t *const theirs = reinterpret_cast<const float4_t *>(ring + at + (uint32_t)(wave ^ 4) * 4096u);
 #pragma unroll
-    for (int j = 0; j < kOwn; ++j) last_out[j] = zero4;
-
-    int cp_c = c_first, cp_ku = k0, cp_begin = k0;
-    int cp_end = (c_first == c_last) ? k1 : KU;
-
-    // A segment is complete: the four waves of each column half sum their
-    // tiles in ring slot j, which every pair has read (its refill is issued
-    // after the last barrier here; the other slot may be receiving the next
-    // stage).  Wave (ks, hf) writes into the half of the pair's slot its
-    // own loads fill, in two rounds of eight blocks (column blocks 2r, 2r + 1).
-    auto finish_segment = [&](int j) {
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) mine[(b * 2 + mb) * 64 + lane] = acc[b][2 + mb];
+        lds_barrier();
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) acc[b][mb] += theirs[(b * 2 + mb) * 64 + lane];
+        lds_barrier();
+    };
+    // A segment other than the range's last is complete: write C (whole tile),
+    // or slot 0 (shared first tile) and arrive there.
+    auto finish_segment = [&](uint32_t at) {
+        reduce_halves(at);
         float4_t out[kOwn];
-        const auto area = [&](int k2, int h2) {
-            return reinterpret_cast<float4_t *>(a_lds + (k2 * D + j) * kAStage + h2 * 8192);
-        };
-        float4_t *const mine = area(ks, hf);
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
+        for (int j = 0; j < kOwn; ++j) out[j] = acc[j / 2][j % 2];
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) mine[(c * MB + mb) * 64 + lane] = acc[2 * r + c][mb];
-            lds_barrier();
-#pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const int at = (c * MB + ks) * 64 + lane;
-                float4_t s = area(0, hf)[at];
-#pragma unroll
-                for (int k2 = 1; k2 < KS; ++k2) s += area(k2, hf)[at];
-                out[2 * r + c] = s;
-            }
-            lds_barrier();
-        }
-#pragma unroll
-        for (int b = 0; b < NBW; ++b)
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb) acc[b][mb] = zero4;
-        if (cp_begin == 0 && cp_end == KU) {
-            store_c(cp_c, out);
-        } else if (cp_c == c_last) {
-            has_last = true;
+        if (cp_begin != 0 || cp_end != KU) {
+            int l = lane;
+            asm volatile("" : "+v"(l));
 #pragma unroll
-            for (int j2 = 0; j2 < kOwn; ++j2) last_out[j2] = out[j2];
+            for (int j = 0; j < kOwn; ++j) store_partial16(my_slots, own(j), l, out[j]);
+            wait_vmcnt<0>();
+            reduce_first = arrive_by_wave(p, cp_c, wave, grid, l);
         } else {
-            has_first = true;
-#pragma unroll
-            for (int j2 = 0; j2 < kOwn; ++j2) store_partial(my_slots, own(j2), lane, out[j2]);
+            store_c(cp_c, out);
         }
     };
 
-    auto step = [&](int j, int st, int later) {
-        if (st < n_st) {
-            compute(j, later, cp_ku + ks < cp_end);
-            if (cp_ku + KS >= cp_end) {
-                if (cp_c != c_last) {  // the last segment is closed after the loop
-                    finish_segment(j);
-                    cp_c += 1;
-                    cp_ku = 0;
-                    cp_begin = 0;
-                    cp_end = (cp_c < c_last) ? KU : k1;
-                }
-            } else {
-                cp_ku += KS;
-            }
-        }
-    };
-    const int st_last = (n_st - 1) / D * D;
-    for (int st0 = 0; st0 < st_last; st0 += D) {
+    // Stage 0's operands.
+    wait_vmcnt<(P - 1) * kLoads>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
 #pragma unroll
-        for (int j = 0; j < D; ++j) {
-            step(j, st0 + j, D - 1);
-            issue(j);
-            advance_ld();
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) read_a(t, mb);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        read_w(b);
+        if constexpr (!PER_CHANNEL) read_s(b);
+    }
+    wait_lgkmcnt0();
+#pragma unroll
+    for (int t = 0; t < 4; ++t) landed_a(t);
+    landed_ws();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) wv[b] = wn_[b];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) nx[q] = pair_quarter<!PER_CHANNEL>(wv[0][0], q, s2[0], dq);
+    // k-steps 0 and 1 of stage 0
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const half8_t w = operand();
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) slot(t, b, mb, w, b == 0 ? wv[1][t] : wv[0][t + 1], s2[1 - b]);
+        }
+
+    for (int st = 0; st + 1 < n_st; ++st) {
+        // Stage st + 1 has landed (P - 2 stages were issued after it), and
+        // every wave holds the rest of stage st in registers.
+        wait_lgkmcnt0();
+        wait_vmcnt<(P - 2) * kLoads>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        landed_a(2);
+        landed_a(3);
+        const uint32_t old_slot = rd_slot;
+        rd_slot = rd_slot == (uint32_t)((P - 1) * kStage) ? 0u : rd_slot + (uint32_t)kStage;
+        // k-steps 2 and 3 of stage st; reads stage st + 1's words, scales and first rows
+        constexpr int kFirst = PER_CHANNEL ? NB : 2 * NB;  // reads before the rows
+#pragma unroll
+        for (int t = 2; t < 4; ++t)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const half8_t w = operand();
+                if (t == 3 && b == 1) {
+                    wait_lgkmcnt_n(12 - kFirst);  // the words and scales
+                    landed_ws();
+                }
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const int k = ((t - 2) * NB + b) * MB + mb;
+                    slot(t, b, mb, w, b == 0 ? wv[1][t] : t == 2 ? wv[0][3] : wn_[0][0], s2[1 - b]);
+                    if (k < NB) read_w(k);
+                    else if (k < kFirst) read_s(k - NB);
+                    else if (k < kFirst + 2 * MB) read_a((k - kFirst) / MB, (k - kFirst) % MB);
+                }
+            }
+        wait_lgkmcnt0();
+        landed_a(0);
+        landed_a(1);
+#pragma unroll
+        for (int b = 0; b < NB; ++b) wv[b] = wn_[b];
+        // stage st was its segment's last?
+        if (cp_ku + KS >= cp_end) {
+            finish_segment(old_slot);
+            cp_c += 1;
+            cp_ku = 0;
+            cp_begin = 0;
+            cp_end = end_of(cp_c);
+        } else {
+            cp_ku += KS;
+        }
+        // k-steps 0 and 1 of stage st + 1; refills stage st's slot and reads the last rows
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const half8_t w = operand();
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb) {
+                    const int k = (t * NB + b) * MB + mb;
+                    slot(t, b, mb, w, b == 0 ? wv[1][t] : wv[0][t + 1], s2[1 - b]);
+                    if (k < 2 * MB) read_a(2 + k / MB, k % MB);
+                    if ((k & 1) && k / 2 < kLoads) issue(k / 2);
+                }
+            }
+        advance_ld();
+    }
+    wait_lgkmcnt0();
+    landed_a(2);
+    landed_a(3);
+    // k-steps 2 and 3 of the last stage
+#pragma unroll
+    for (int t = 2; t < 4; ++t)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const half8_t w = operand();
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) slot(t, b, mb, w, b == 0 ? wv[1][t] : wv[0][3], s2[1 - b]);
+        }
+    wait_vmcnt<0>();
+    lds_barrier();
+    reduce_halves(0);
+
+    // The last segment: whole, or the range's last tile (shared), whose sums
+    // this wave adds from its registers if it completes the tile.
+    float4_t last_out[kOwn], out[kOwn];
+#pragma unroll
+    for (int j = 0; j < kOwn; ++j) last_out[j] = acc[j / 2][j % 2];
+    if (cp_begin == 0 && cp_end == KU) {
+        store_c(cp_c, last_out);
+    } else {
+#pragma unroll
+        for (int j = 0; j < kOwn; ++j) store_partial16(my_slots + kSlotFloats, own(j), lane, last_out[j]);
+        wait_vmcnt<0>();
+        if (arrive_by_wave(p, cp_c, wave, grid, lane)) {
+            reduce_by_wave<kOwn>(p, cp_c, grid, kSlotFloats, lane, own, wg, last_out, out);
+            store_c(cp_c, out);
         }
     }
-#pragma unroll
-    for (int j = 0; j < D; ++j) step(j, st_last + j, D - 1 - j);
-    // Stages past the range were issued (through empty descriptors) but never
-    // waited for: each wave drains its own before the ring is reused (a wave
-    // writes only where its own loads land).
-    wait_vmcnt<0>();
-    finish_segment(0);
-
-    auto own_slot = [&](int j) { return own(j); };
-    combine_tiles<kOwn>(p, flags, wg, grid, kSlotFloats, lane, has_first, c_first, has_last, c_last, last_out,
-                        own_slot, store_c);
+    if (reduce_first) {
+        reduce_by_wave<kOwn>(p, c_begin, grid, kSlotFloats, lane, own, -1, last_out, out);
+        store_c(c_begin, out);
+    }
 }
 
 }  // namespace
+
+namespace marlin {
 
 hipError_t launch_pair_gemm(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream)
 {
