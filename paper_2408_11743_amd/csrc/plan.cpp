@@ -268,6 +268,86 @@ TilePartition best_tile_partition(const Override &ov, int64_t tiles, int KU, int
     }
     return best;
 }
+
+// Stream kernel, dense and 2:4 sparse, up to 64 rows: the time of a launch is
+// a fixed cost, plus per 128-row block of the busiest work-group a unit time
+// (kStreamUnit: by sparsity, rows and tile shape) that grows with the share of
+// the compute units in use, plus what the partition adds: per tile of a
+// work-group beyond its first, per split tile (combination; per contributor
+// the reducer reads one partial tile) and, for ranges that do not end on tile
+// boundaries, a second segment with its own partial tile and arrival.  z is the
+// partial tile's size in units of 8 KiB.  One fit to 4509 timings on 43 layer
+// shapes at 1, 8, 16, 32 and 64 rows (5% rms; the configuration it picks is
+// within 1.5% of the best one timed, geometric mean).
+constexpr double kStreamFixedUs = 2.90, kStreamFixedPerZUs = 0.88;
+constexpr double kStreamTileUs = 0.45;
+constexpr double kStreamSplitUs = 1.56, kStreamContributorPerZUs = 0.31;
+constexpr double kStreamRaggedUs = 1.61, kStreamRaggedPerZUs = 2.00;
+// A split has to be ahead of whole tiles by more than the fit's error on small layers.
+constexpr double kStreamSplitWeight = 1.04;
+// ... and another configuration of the first choice: 2048 x 2048 at 64 rows, eight
+// or four waves, are 5.3 us both by the fit and measure 5.2 and 5.7 us.
+constexpr double kStreamFirstChoiceWeight = 0.96;
+struct StreamUnit {
+    double unit_us, unit_busy_us;  // zero: no such kernel
+};
+constexpr StreamUnit kStreamUnit[2][4][8] = {
+    // nb, waves: 8,8; 8,4; 4,8; 4,4; 2,8; 2,4; 1,8; 1,4
+    {{{0.168, 0.120}, {0.171, 0.144}, {0.074, 0.061}, {0.104, 0.040},
+      {0.039, 0.032}, {0.077, 0.008}, {0.032, 0.014}, {0.061, 0.009}},
+     {{0.184, 0.110}, {0.178, 0.145}, {0.099, 0.052}, {0.109, 0.045},
+      {0.053, 0.037}, {0.087, 0.012}, {0.045, 0.018}, {0.071, 0.005}},
+     {{0.207, 0.116}, {0.204, 0.149}, {0.127, 0.054}, {0.138, 0.050},
+      {0.075, 0.046}, {0.099, 0.025}, {0.070, 0.018}, {0.088, 0.003}},
+     {{0.0, 0.0}, {0.283, 0.097}, {0.0, 0.0}, {0.175, 0.054},
+      {0.0, 0.0}, {0.142, 0.027}, {0.095, 0.043}, {0.115, 0.022}}},
+    {{{0.0, 0.0}, {0.0, 0.0}, {0.064, 0.037}, {0.094, 0.027},
+      {0.035, 0.028}, {0.071, 0.012}, {0.033, 0.027}, {0.058, 0.009}},
+     {{0.0, 0.0}, {0.0, 0.0}, {0.083, 0.032}, {0.106, 0.022},
+      {0.051, 0.033}, {0.081, 0.014}, {0.053, 0.027}, {0.069, 0.015}},
+     {{0.0, 0.0}, {0.0, 0.0}, {0.108, 0.038}, {0.125, 0.033},
+      {0.076, 0.038}, {0.103, 0.024}, {0.075, 0.035}, {0.090, 0.023}},
+     {{0.0, 0.0}, {0.234, 0.059}, {0.0, 0.0}, {0.152, 0.035},
+      {0.0, 0.0}, {0.129, 0.028}, {0.103, 0.050}, {0.116, 0.037}}},
+};
+StreamUnit stream_unit(bool sparse, int mb, int ar, int nb, int waves)
+{
+    const int row = mb == 2 ? 3 : ar == 4 ? 2 : ar == 2 ? 1 : 0;
+    const int col = (nb == 8 ? 0 : nb == 4 ? 2 : nb == 2 ? 4 : 6) + (waves == 4);
+    return kStreamUnit[sparse ? 1 : 0][row][col];
+}
+
+// Whole tiles; each tile split evenly over up to 16 work-groups, whose ranges
+// then end on tile boundaries (one segment and one partial tile each:
+// 8192 x 10240 at 32 rows, 80 column tiles of 128: 16.5 us as 240 thirds of
+// tiles, 21.9 as 256 equal ranges of 20 blocks); or equal ranges over all work-groups.
+Partition best_stream_partition(int64_t tiles, int KU, int64_t grid, int z8, const StreamUnit &u, size_t slot_bytes,
+                                size_t budget, const Partition *first_choice)
+{
+    Partition best{1e30, 0, 1};
+    const double z = (double)z8 / 8.0, fixed = kStreamFixedUs + kStreamFixedPerZUs * z;
+    auto take = [&](double t, int whole, int64_t g) {
+        if (!whole && budget != SIZE_MAX && kCounterRegionBytes + (size_t)g * slot_bytes > budget) return;
+        t = (fixed + t) * (whole ? 1.0 : kStreamSplitWeight);
+        if (first_choice && first_choice->whole == whole && first_choice->grid == g) t *= kStreamFirstChoiceWeight;
+        if (t < best.t) best = {t, whole, g};
+    };
+    auto unit = [&](int64_t active) { return u.unit_us + u.unit_busy_us * (double)active / (double)kMaxCus; };
+    const int64_t rounds = (tiles - 1) / grid, rem = tiles - rounds * grid;  // rem: work-groups with one tile more
+    take((double)KU * ((double)rounds * unit(grid) + unit(rem)) + (double)rounds * kStreamTileUs, 1,
+         tiles < grid ? tiles : grid);
+    for (int64_t s = 2; s <= KU && s <= 16 && tiles * s <= grid; ++s)
+        take((double)((KU + s - 1) / s) * unit(tiles * s) + kStreamSplitUs + kStreamContributorPerZUs * z * (double)s,
+             0, tiles * s);
+    const int64_t units = tiles * KU, g = grid < units ? grid : units;
+    if (g % tiles != 0 && tiles % g != 0) {
+        const double per = (double)units / (double)g;
+        take((double)((units + g - 1) / g) * unit(g) + kStreamSplitUs + kStreamRaggedUs + kStreamRaggedPerZUs * z +
+                 kStreamContributorPerZUs * z * (1.0 + (double)KU / per),
+             0, g);
+    }
+    return best;
+}
 }  // namespace
 
 GemmConfig choose_config(int M, int N, int K, int group_units, int cus, bool sparse, const Override &ov,
@@ -450,6 +530,36 @@ GemmConfig choose_config(int M, int N, int K, int group_units, int cus, bool spa
                 cfg.whole = pt.whole;
                 cfg.hybrid = pt.hybrid;
                 best_grid = pt.grid;
+            }
+        }
+    }
+    // Row groups of 16 and 32 up to 64 rows: the tile width, waves and
+    // partition again, by the finer fit (the choice of kernel above is left as
+    // it is; beyond 64 rows the two agree within their errors).  It changes one
+    // in four calls drawn over K and N of 1024 to 28672 and 1 to 64 rows, dense
+    // and sparse: 110 of those measured 1.24 times as fast in the geometric
+    // mean (0.98 to 1.58); 8192 x 8192 at 32 rows, 14.7 us as 256 ranges of
+    // 128-column tiles, 12.7 us as halves of 64-column tiles.
+    if (cfg.kind == kKindStream && cfg.nb != 0 && cfg.mb <= 2 && M <= 64 && ov.whole < 0 && ov.grid == 0) {
+        const Partition first{0.0, cfg.whole, best_grid};
+        const int first_nb = cfg.nb, first_waves = cfg.waves;
+        double best_us = 1e30;
+        for (int waves = 8; waves >= 4; waves -= 4) {
+            if (ov.waves && waves != ((ov.waves == 8 && cfg.mb == 2 && ov.nb > 1) ? 4 : ov.waves)) continue;
+            for (int nb = 8; nb >= 1; nb >>= 1) {
+                const StreamUnit u = stream_unit(sparse, cfg.mb, cfg.ar, nb, waves);
+                if (tiles16 % nb != 0 || u.unit_us <= 0.0 || (ov.nb && nb != ov.nb)) continue;
+                const Partition pt =
+                    best_stream_partition((int64_t)(tiles16 / nb) * cfg.rg, KU, grid, nb * cfg.mb, u,
+                                          (size_t)2 * nb * cfg.mb * 256 * sizeof(float), partial_budget,
+                                          nb == first_nb && waves == first_waves ? &first : nullptr);
+                if (pt.t < best_us) {
+                    best_us = pt.t;
+                    cfg.nb = nb;
+                    cfg.waves = waves;
+                    cfg.whole = pt.whole;
+                    best_grid = pt.grid;
+                }
             }
         }
     }
