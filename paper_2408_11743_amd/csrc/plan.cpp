@@ -1,4 +1,4 @@
-// Launch planning (see plan.h): a cost model of the two GEMM kernels fitted
+// Launch planning (see plan.h): cost models of the GEMM kernels fitted
 // to MI355X measurements, the striped partition (Section 3.4, "Striped
 // Partitioning": whole column tiles per work-group, or Stream-K ranges of
 // 128-row blocks combined across work-groups), workspace sizing, and a memo
@@ -82,9 +82,10 @@ size_t workspace_bytes_used(const GemmConfig &cfg) { return cfg.whole ? 0 : work
 // group arrive in LDS; 4 or (one row block, or one column block) 8 waves
 // split K, kStreamOcc work-groups per CU.
 //
-// Column tile width (nb 16-column blocks), waves and partition come from a
-// cost model fitted to MI355X measurements (218 whole-tile timings over the
-// Llama-7B and 70B layer shapes, 4% rms): a fixed cost per launch, plus the
+// The kernel, and beyond 64 rows the stream kernel's column tile width (nb
+// 16-column blocks), waves and partition, come from a cost model fitted to
+// MI355X measurements (218 whole-tile timings over the Llama-7B and 70B layer
+// shapes, 4% rms): a fixed cost per launch, plus the
 // larger of the busiest work-group's weight bytes over its streaming rate
 // (which depends on the tile width, the rows of A and the waves: narrow tiles
 // and more rows cost more instructions per weight byte) and the layer's

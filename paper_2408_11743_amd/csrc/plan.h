@@ -15,7 +15,7 @@ constexpr int kStreamOcc = 1;  // stream kernel work-groups per compute unit
 constexpr int kKindStream = 0;  // w4a16_stream_kernel (any M; row groups of 32)
 constexpr int kKindTile = 1;    // w4a16_tile_kernel (activation tile shared by the waves)
 constexpr int kKindTile8 = 3;   // w4a16_tile_kernel of tile8.hip (every operand through LDS, two waves per SIMD)
-constexpr int kKindWide = 2;    // w4a16_wide_kernel (four waves along N, weights in registers)
+constexpr int kKindWide = 2;    // w4a16_wide_kernel (128 x 256 tiles, group scales on the fp16 weights)
 
 // One launch configuration of the GEMM kernel.
 //   mb   : 16-row blocks of A per row group (1, 2, or 4: 128-column dense tiles
@@ -101,7 +101,7 @@ inline bool tile_config_supported(int nw, int wm, int mbw, int nbw, int ks)
 
 // Tuning and test override of the configuration (the cost model is the
 // default): MARLIN_FORCE_CONFIG="nb=<1|2|4|8>,grid=<n>,whole=<0|1>,
-// kind=<stream|tile|wide>,waves=<4|8>,nw=<4|8>,ks=<1|2|4>,mb=<1|2|4>" forces
+// kind=<stream|tile|tile8|wide>,waves=<4|8>,nw=<4|8>,ks=<1|2|4>,mb=<1|2|4>" forces
 // the column-tile width, the work-group count, the partition, the kernel, the
 // stream kernel's waves per work-group, the tile kernel's waves and blocks
 // per stage and the stream kernel's 16-row blocks per row group, where the
