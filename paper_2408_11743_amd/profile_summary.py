@@ -81,8 +81,8 @@ def counter_per_dispatch(pmc_dir: str, counter: str) -> list[tuple[str, float]]:
 def short(name: str) -> str:
     """'void marlin::(anonymous namespace)::w4a16_stream_kernel<1, 1, 8, 1, false>(...)' -> 'w4a16_stream_kernel<1, 1, 8, 1, false>'."""
     base = name.replace("(anonymous namespace)::", "").replace("void ", "", 1)
-    base = base.split("(")[0].strip()
-    return base.split("::")[-1]
+    head, bracket, args = base.split("(")[0].strip().partition("<")
+    return head.split("::")[-1] + bracket + args.replace("marlin::", "").replace("> >", ">>")
 
 
 def dispatch_runs(trace_dir: str, prefix: str, gap_ns: int = 20_000_000) -> list:
@@ -116,7 +116,7 @@ def quantize_summary(a, bench: dict) -> None:
     """Kernel trace of bench.py --quantize-only: one row per shape."""
     import paper_2408_11743_amd.roofline as R
     cases = bench["quantize"]["per_shape"]
-    runs = dispatch_runs(a.trace, "quantize_kernel")
+    runs = dispatch_runs(a.trace, "quantize128_kernel")
     if len(runs) != len(cases):
         raise SystemExit("%d quantiser runs in the trace for %d cases" % (len(runs), len(cases)))
     md = ["# Kernel trace: weight quantiser, g = 128, clipping search over %d ratios" % cases[0]["ratios"], "",
@@ -156,7 +156,7 @@ def quantize_counter_summary(a, bench: dict) -> None:
     per = {}
     with open(_one(os.path.join(a.pmc, "**", "*counter_collection.csv"))) as f:
         for r in csv.DictReader(f):
-            if not short(r["Kernel_Name"]).startswith("quantize_kernel"):
+            if not short(r["Kernel_Name"]).startswith("quantize128_kernel"):
                 continue
             d = per.setdefault(int(r["Dispatch_Id"]), {"grid": int(r["Grid_Size"])})
             d[r["Counter_Name"]] = d.get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
