@@ -114,14 +114,14 @@ FP32_VECTOR_FLOPS = 157.3e12
 FP32_LANE_OPS = VALU_LANE_OPS
 
 # Vector instructions per weight (lane operations) of the built g = 128
-# quantiser kernel: 12.35 outside the search (loading, magnitude maximum,
-# the final scale's reciprocal and codes) and 7.21 per clipping ratio
-# (scale multiply, round, clamp, multiply back, subtract, square,
-# accumulate), counted in its gfx950 assembly: 1580 + 923 per ratio, for the
-# 128 weights a thread owns.  The counters give 83.7 per weight at 10 ratios
-# (branches skip a few), against 84.5 by this count.
-QUANT_VALU_BASE = 1580 / 128
-QUANT_VALU_PER_RATIO = 923 / 128
+# quantiser kernel: 8.70 outside the search (loading, magnitude maximum,
+# the final scale's reciprocal and codes) and 6.23 per clipping ratio
+# (scale multiply, round, clamp, fused difference, square and accumulate),
+# counted in its gfx950 assembly: 1114 + 798 per ratio, for the
+# 128 weights a thread owns.  The counters give 71.04 per weight at 10 ratios,
+# as this count does.
+QUANT_VALU_BASE = 1114 / 128
+QUANT_VALU_PER_RATIO = 798 / 128
 QUANT_VALU_PER_WEIGHT_G128_10 = QUANT_VALU_BASE + 10 * QUANT_VALU_PER_RATIO
 
 
