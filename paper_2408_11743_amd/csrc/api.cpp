@@ -116,11 +116,13 @@ marlin_status_t marlin::gemm_entry(const uint16_t *A, const void *w_packed, cons
         p.G = (int)G;
         p.KU = (int)(K / 128);
         p.rg = cfg.rg;
-        p.tiles = (int)((N + tile_cols(cfg) - 1) / tile_cols(cfg)) * cfg.rg;
-        p.units = (cfg.hybrid ? p.tiles % cfg.grid : p.tiles) * p.KU;
-        p.gran = cfg.whole ? p.KU : 1;
-        p.per_wg = (p.units / p.gran) / cfg.grid;
-        p.extra = (p.units / p.gran) % cfg.grid;
+        const Ranges r = ranges_of(cfg, (int)N, (int)K);
+        if (r.per_wg < 1) return MARLIN_ERR_INVALID_ARGUMENT;  // the planner never asks for it
+        p.tiles = r.tiles;
+        p.units = r.units;
+        p.gran = r.gran;
+        p.per_wg = r.per_wg;
+        p.extra = r.extra;
         p.group_units = gu;
         // Exact for every block index below 2^13 (K <= 2^20): with
         // e = gmagic * gu - 2^26 < gu <= 2^13, ku * e < 2^26.
@@ -160,7 +162,7 @@ marlin_status_t describe_impl(int64_t M, int64_t N, int64_t K, int64_t group, ch
     if (buf_bytes > 0)
         snprintf(buf, buf_bytes, "%s cols=%d rg=%d partition=%s grid=%d", name,
                  tile_cols(cfg), cfg.rg,
-                 cfg.whole ? "whole" : "streamk", cfg.grid);
+                 cfg.hybrid ? "hybrid" : cfg.whole ? "whole" : "streamk", cfg.grid);
     return MARLIN_OK;
 }
 }  // namespace

@@ -232,8 +232,8 @@ struct TilePartition {
 // ends then fall on tile boundaries, so every work-group has one segment and
 // writes one partial tile: measured 68 against 75 us for unaligned Stream-K
 // ranges on 8192 x 28672 at M = 128); or, with more tiles than work-groups,
-// the hybrid: a multiple of the work-groups whole, the rest shared by all of
-// them, first, so that their combination is not what every work-group ends on
+// the hybrid: a multiple of the work-groups whole, the rest (at least as many
+// blocks as work-groups) shared by all of them, first, so that their combination is not what every work-group ends on
 // (8192 x 10240 at M = 1024: 159 us, against 173 for Stream-K and 194 whole).
 TilePartition best_tile_partition(const Override &ov, int64_t tiles, int KU, int64_t grid, const TileFit &f,
                                   size_t slot_bytes, size_t budget)
@@ -246,7 +246,9 @@ TilePartition best_tile_partition(const Override &ov, int64_t tiles, int KU, int
     const int64_t rounds = tiles / grid, rem = tiles % grid;
     const double busy = f.unit_us + f.unit_busy_us;  // unit time with every compute unit in use
     auto unit = [&](int64_t active) { return f.unit_us + f.unit_busy_us * (double)active / (double)kMaxCus; };
-    const bool hybrid = rounds > 0 && rem != 0;
+    // every work-group needs a block of the shared tiles: one without never
+    // arrives at a tile that counts on it (ranges_of, plan.h)
+    const bool hybrid = rounds > 0 && rem * KU >= grid;
     if (ov.whole < 0 || ov.whole == 1 || (ov.whole == 2 && !hybrid)) {
         const int64_t n = rounds + (rem != 0);
         take(f.fixed_us + (double)KU * ((double)rounds * busy + (rem ? unit(rem) : 0.0)) + (double)(n - 1) * f.tile_us,

@@ -54,6 +54,26 @@ inline int tile_cols(const GemmConfig &c)
 }
 inline int tile_rows(const GemmConfig &c) { return c.kind == kKindTile || c.kind == kKindTile8 ? c.tile_wm * 16 * c.mb : 16 * c.mb; }
 
+// How a launch deals N columns of K to its work-groups: `units` 128-row blocks
+// (of every tile, or of the hybrid's shared tiles) in items of `gran`, per_wg
+// items each and one more for `extra` of them.  per_wg >= 1: a work-group
+// without a share of the ranges never arrives at a tile, but those between a
+// tile's first and last contributor are counted on (device.h).
+struct Ranges {
+    int tiles, units, gran, per_wg, extra;
+};
+inline Ranges ranges_of(const GemmConfig &c, int N, int K)
+{
+    Ranges r;
+    const int KU = K / 128;
+    r.tiles = (N + tile_cols(c) - 1) / tile_cols(c) * c.rg;
+    r.units = (c.hybrid ? r.tiles % c.grid : r.tiles) * KU;
+    r.gran = c.whole ? KU : 1;
+    r.per_wg = r.units / r.gran / c.grid;
+    r.extra = r.units / r.gran % c.grid;
+    return r;
+}
+
 // ceil(2^32 / d) for 2 <= d: with it, floor(n / d) = floor(n * m / 2^32) for
 // every n with n * d <= 2^32 (m = (2^32 + e) / d, 0 <= e < d, so the error
 // n * e / (d 2^32) stays below 1/d).  0 when d < 2.

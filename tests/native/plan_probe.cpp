@@ -23,6 +23,17 @@ uint64_t probe_plan(int M, int N, int K, int gu, int cus, int sparse, uint64_t w
     return (uint64_t)workspace_bytes_used(c);
 }
 
+// The same for the partition: out: kind, whole, hybrid, grid, then the dealing
+// (ranges_of): tiles, units, gran, per_wg, extra.  force: an override's text,
+// or NULL.
+void probe_partition(int M, int N, int K, int gu, int cus, uint64_t ws, const char *force, int *out)
+{
+    const GemmConfig c = plan_pass(M, N, K, gu, cus, false, (size_t)ws, parse_override(force));
+    const Ranges r = ranges_of(c, N, K);
+    const int v[9] = {c.kind, c.whole, c.hybrid, c.grid, r.tiles, r.units, r.gran, r.per_wg, r.extra};
+    for (int i = 0; i < 9; ++i) out[i] = v[i];
+}
+
 uint64_t probe_required(int64_t M, int N, int K, int gu) { return (uint64_t)required_workspace(M, N, K, gu, Override{}); }
 
 // Nanoseconds per planning of one call (the override read, the workspace

@@ -50,21 +50,53 @@ def test_eight_wave_kernels(mk, monkeypatch, kind, part, K, N, g):
     assert int(ws.buf[: 1 << 20].view(torch.int32).abs().max()) == 0
 
 
-@pytest.mark.parametrize("K,N,M", [(1024, 10240, 500), (512, 4160, 2100)])
-def test_hybrid_in_a_replayed_graph(mk, K, N, M):
-    # the library's own choice, repeated in a graph, equals the eager result bit for bit
-    q, s = synth.weights(22, K, N, 128)
-    wp, sp = mk.pack(torch.from_numpy(q).cuda(), torch.from_numpy(s).cuda(), group=128)
-    A = torch.from_numpy(synth.activations(22, M, K)).cuda()
-    ws = mk.Workspace("cuda")
+def problem(mk, K, N, M, g=128):
+    q, s = synth.weights(22, K, N, None if g == -1 else g)
+    wp, sp = mk.pack(torch.from_numpy(q).cuda(), torch.from_numpy(s).cuda(), group=g)
+    A = synth.activations(22, M, K)
+    ws = mk.Workspace("cuda", mk.marlin_workspace_bytes(M, N, K, g))
+    return torch.from_numpy(A).cuda(), wp, sp, ws, oracle.gemm(A, q, s, g)
+
+
+def check(out, ref, ws, what):
+    got = out.cpu().numpy().astype(np.float64)
+    bad = ~(np.abs(got - ref) <= 2e-3 + 1e-2 * np.abs(ref))  # an output nobody wrote is NaN
+    assert not bad.any(), "%s: %d wrong, first at %s" % (what, bad.sum(), np.argwhere(bad)[:3])
+    assert int(ws.buf[: 1 << 20].view(torch.int32).abs().max()) == 0, what
+
+
+@pytest.mark.parametrize("K,N,M,g", [(4096, 11008, 353, 128), (4096, 11008, 705, -1), (4096, 11008, 1409, 128),
+                                     (4096, 11008, 2177, 128), (5120, 5120, 800, -1), (3584, 18944, 400, 128),
+                                     (4096, 22016, 129, 128), (4096, 11008, 1000, 128), (1024, 28672, 700, -1)])
+def test_few_tiles_left_over(mk, monkeypatch, K, N, M, g):
+    # the library's own choice at row counts with from one to a few tiles more
+    # than a multiple of the work-groups, then the same workspace again
+    monkeypatch.delenv("MARLIN_FORCE_CONFIG", raising=False)
+    A, wp, sp, ws, ref = problem(mk, K, N, M, g)
+    d = mk.marlin_describe(M, N, K, g)
+    for _ in range(2):
+        out = torch.full((M, N), float("nan"), dtype=torch.float16, device="cuda")
+        mk.gemm(A, wp, sp, K, N, group=g, out=out, workspace=ws)
+        check(out, ref, ws, "%s M=%d" % (d, M))
+
+
+@pytest.mark.parametrize("K,N,M", [(4096, 11008, 1000), (8192, 10240, 1000)])
+def test_hybrid_in_a_replayed_graph(mk, monkeypatch, K, N, M):
+    # the library's own choice, repeated in a graph, is right at every replay
+    # and equals the eager result bit for bit
+    monkeypatch.delenv("MARLIN_FORCE_CONFIG", raising=False)
+    assert "partition=hybrid" in mk.marlin_describe(M, N, K, 128)
+    A, wp, sp, ws, ref = problem(mk, K, N, M)
     first = mk.gemm(A, wp, sp, K, N, workspace=ws).clone()
+    check(first, ref, ws, "eager")
     out = torch.empty_like(first)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
         mk.gemm(A, wp, sp, K, N, out=out, workspace=ws)
     for _ in range(3):
-        out.zero_()
+        out.fill_(float("nan"))
         graph.replay()
         assert torch.equal(out, first)
         assert torch.equal(mk.gemm(A, wp, sp, K, N, workspace=ws), first)
+    check(out, ref, ws, "replayed")
