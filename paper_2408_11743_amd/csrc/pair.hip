@@ -364,7 +364,7 @@ __global__ void __launch_bounds__(512, 1) w4a16_pair_kernel(GemmProblem p)
             for (int b = 0; b < NB; ++b) {
                 const half8_t w = operand();
                 if (t == 3 && b == 1) {
-                    wait_lgkmcnt_n(12 - kFirst);  // the words and scales
+                    wait_lgkmcnt_n(2 * MB);  // the words and scales: the rows' reads come after them
                     landed_ws();
                 }
 #pragma unroll
