@@ -348,12 +348,9 @@ __global__ void __launch_bounds__(512, 1) w4a16_pair_kernel(GemmProblem p)
     for (int st = 0; st + 1 < n_st; ++st) {
         // Stage st + 1 has landed (P - 2 stages were issued after it), and
         // every wave holds the rest of stage st in registers.
-        wait_lgkmcnt0();
         wait_vmcnt<(P - 2) * kLoads>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        landed_a(2);
-        landed_a(3);
         const uint32_t old_slot = rd_slot;
         rd_slot = rd_slot == (uint32_t)((P - 1) * kStage) ? 0u : rd_slot + (uint32_t)kStage;
         // k-steps 2 and 3 of stage st; reads stage st + 1's words, scales and first rows
@@ -405,11 +402,11 @@ __global__ void __launch_bounds__(512, 1) w4a16_pair_kernel(GemmProblem p)
                     if ((k & 1) && k / 2 < kLoads) issue(k / 2);
                 }
             }
+        wait_lgkmcnt0();  // read in the first k-step
+        landed_a(2);
+        landed_a(3);
         advance_ld();
     }
-    wait_lgkmcnt0();
-    landed_a(2);
-    landed_a(3);
     // k-steps 2 and 3 of the last stage
 #pragma unroll
     for (int t = 2; t < 4; ++t)

@@ -247,10 +247,10 @@ __global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
 #pragma unroll
         for (int mb = 0; mb < MB; ++mb) asm volatile("" : "+v"(av[t][mb]));
     };
-    auto landed_ws = [&]() {
+    auto landed_ws = [&](int words) {
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            asm volatile("" : "+v"(wv[b]));
+            if (b < words) asm volatile("" : "+v"(wv[b]));
             if constexpr (!PER_CHANNEL) asm volatile("" : "+v"(sv[b]));
         }
     };
@@ -372,7 +372,7 @@ __global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
     wait_lgkmcnt0();
     landed_a(0);
     landed_a(1);
-    landed_ws();
+    landed_ws(NB);
     scales();
 #pragma unroll
     for (int q = 0; q < 4; ++q) nx[q] = wide_quarter<!PER_CHANNEL>(wv[0][0], q, s2[0], dq);
@@ -388,11 +388,9 @@ __global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
     for (int st = 0; st + 1 < n_st; ++st) {
         // Stage st + 1 has landed (P - 2 stages were issued after it), and
         // every wave holds the rest of stage st in registers.
-        wait_lgkmcnt0();
         wait_vmcnt<(P - 2) * kLoads>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        landed_a(1);
         const uint32_t old_slot = rd_slot;
         rd_slot = rd_slot == (uint32_t)((P - 1) * kStage) ? 0u : rd_slot + (uint32_t)kStage;
         // second k-step of stage st; reads stage st + 1's first rows, words and scales
@@ -402,7 +400,7 @@ __global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
             if (b == NB - 1) {
                 wait_lgkmcnt_n(1);  // all but word 3
                 landed_a(0);
-                landed_ws();
+                landed_ws(NB - 1);
                 scales();
             }
 #pragma unroll
@@ -441,10 +439,10 @@ __global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
                 if (k % 4 == 1 && k / 4 < kLoads) issue(k / 4);
             }
         }
+        wait_lgkmcnt0();  // read three column blocks ago
+        landed_a(1);
         advance_ld();
     }
-    wait_lgkmcnt0();
-    landed_a(1);
     // second k-step of the last stage
 #pragma unroll
     for (int b = 0; b < NB; ++b) {

@@ -3,7 +3,8 @@ and wait for them by hand (s_waitcnt lgkmcnt), so the compiler does not know
 when their registers are written.  This test compiles the kernels for gfx950
 and follows every path through their assembly, branches and back edges
 included: no instruction may touch a register that an LDS read still in flight
-is going to write.
+is going to write, and no read from inline assembly may be in flight at a
+branch, where the compiler places the moves of values that change registers.
 
 LDS operations complete in order, so a wait for a count of n leaves the n
 newest; scalar loads share the counter and may complete in any order, so while
@@ -20,6 +21,10 @@ from paper_2408_11743_amd import build as B
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2408_11743_amd", "csrc")
 SMEM = "smem"
+
+
+class AsmRead(frozenset):
+    """Registers of an LDS read that the compiler does not know as one."""
 
 
 def registers(text):
@@ -91,12 +96,15 @@ def walk(lines, labels):
             if line.op.startswith("s_load") or line.op.startswith("s_buffer_load"):
                 flight += (SMEM,)
             elif line.op.startswith("ds_"):
-                flight += (line.dest,)
+                flight += (AsmRead(line.dest) if line.asm else line.dest,)
             assert len(seen) < 200000
             if len(flight) > 64:
                 bad.append("line %d: %s is one of 65 operations nobody waits for" % (at, line.text))
                 break
             if line.target:
+                pending = sum(isinstance(f, AsmRead) for f in flight)
+                if pending:
+                    bad.append("line %d: %s with %d reads in flight" % (at, line.text, pending))
                 todo.append((labels[line.target], flight))
                 if line.op == "s_branch":
                     break
@@ -137,6 +145,8 @@ def test_the_walk_finds_a_missing_wait():
     assert len(run(ok.replace("lgkmcnt(1)", "lgkmcnt(2)"))) == 1
     assert len(run(ok.replace("lgkmcnt(0)", "vmcnt(0)"))) == 1
     assert len(run(ok.replace("ds_read_b64 v[4:5], v9", "s_load_dword s0, s[2:3], 0x0"))) == 1  # which of the two is done?
+    mine = ";;#ASMSTART\nds_read_b32 v0, v9\n;;#ASMEND\ns_cbranch_scc1 .LBB0_1\n.LBB0_1:\ns_waitcnt lgkmcnt(0)\ns_endpgm\n"
+    assert run(mine) and not run(mine.replace(";;#ASMEND", ";;#ASMEND\ns_waitcnt lgkmcnt(0)"))
     loop = ".LBB0_1:\ns_waitcnt lgkmcnt(0)\nv_mov_b32_e32 v1, v0\nds_read_b32 v0, v9\nv_mov_b32_e32 v2, v3\n" \
            "s_cbranch_scc1 .LBB0_1\ns_waitcnt lgkmcnt(0)\ns_endpgm\n"
     assert not run(loop)
