@@ -110,6 +110,25 @@ def test_quantize_full_size_sampled_columns(mk, wid, K, N, g):
     check_same(got, want, "K=%d N=%d g=%d sampled columns" % (K, N, g))
 
 
+@pytest.mark.parametrize("K,N,g", [(512, 128, 256), (1408, 64, -1), (256, 64, 128)])
+@pytest.mark.parametrize("ratio", [1.0, 0.55])
+def test_one_ratio_equals_the_same_one_twice(mk, K, N, g, ratio):
+    # a repeated ratio is never better than itself; infinities and NaN leave
+    # no finite error, so their groups get scale 0 and code 8
+    W = synth.fp16_weights(9, K, N)
+    W[5, 0], W[K - 1, 1], W[K // 2, 2], W[:, 3], W[:, 4], W[:, 5] = np.inf, -np.inf, np.nan, 0, 1e-7, -65504.0
+    W[7, 6], W[9, 6] = np.inf, np.nan
+    one, two = gpu_quantize(mk, W, g, (ratio,)), gpu_quantize(mk, W, g, (ratio, ratio))
+    assert np.array_equal(one[0], two[0]) and np.array_equal(one[1].view(np.uint16), two[1].view(np.uint16))
+    rows = K if g == -1 else g
+    for r, c in ((5, 0), (K - 1, 1), (K // 2, 2), (7, 6)):
+        j = r // rows
+        assert one[1][j, c] == 0 and (one[0][j * rows:(j + 1) * rows, c] == 8).all()
+    linear = mk.MarlinLinear.from_float(dev(W.T.copy()), group=g, ratios=(ratio,))
+    wp, sp = mk.pack(dev(one[0]), dev(one[1]), group=g)
+    assert torch.equal(linear.w_packed, wp) and torch.equal(linear.s_packed.view(torch.int16), sp.view(torch.int16))
+
+
 @pytest.mark.parametrize("M,g", [(1, 128), (16, 128), (100, -1)])
 def test_quantized_layer_through_the_gemm(mk, M, g):
     K, N = 2048, 1024
