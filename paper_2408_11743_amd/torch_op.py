@@ -12,8 +12,8 @@ current stream.  There is no autograd formula (inference only).
 
 ``MarlinLinear`` holds one quantised, packed weight matrix and applies it to
 the last dimension of its input, y = x W (no bias).  ``from_float`` takes an
-``nn.Linear``-style fp16 weight [out_features, in_features], quantises it with
-``marlin_quantize`` and packs it with ``marlin_pack_weights``, both on the GPU.
+``nn.Linear``-style fp16 weight [out_features, in_features] and quantises and
+packs it on the GPU, in one launch where it is contiguous (``ops.quantize_linear``).
 
 HIP graphs: the operator enqueues kernels only, so it can be captured.  Its
 workspace is the per-(device, stream) one of ``ops.gemm``, allocated on first
@@ -44,15 +44,17 @@ def _gemm_fake(A, w_packed, s_packed, K, N, group, sparse=False):
     return A.new_empty((A.shape[0], N))
 
 
-def _plain(x: torch.Tensor) -> bool:
-    """Nothing but the CUDA implementation would see the operator's call: no
-    tracing or compiling, no subclass, mode, transform, dual level or profiler,
-    no gradient.  The layer then calls it directly: the operator's dispatch
-    (5 us through Python, 28 -> 12 us a call with the above) is as long as a
-    small decode GEMM."""
+def _plain(x: torch.Tensor, w: torch.Tensor, s: torch.Tensor) -> bool:
+    """Nothing but the CUDA implementation would see the operator's call on
+    these three tensors: no tracing or compiling, no subclass, mode, transform,
+    dual level or profiler, no gradient, no lazily negated view.  The layer then
+    calls it directly: the operator's dispatch (5 us through Python, 28 -> 12 us
+    a call with the above) is as long as a small decode GEMM."""
     return (not torch.compiler.is_compiling()
-            and type(x) is torch.Tensor and x.is_cuda
-            and not (x.requires_grad and torch.is_grad_enabled())
+            and type(x) is torch.Tensor and type(w) is torch.Tensor and type(s) is torch.Tensor
+            and x.is_cuda and w.is_cuda and s.is_cuda
+            and not ((x.requires_grad or s.requires_grad) and torch.is_grad_enabled())
+            and not (x.is_neg() or w.is_neg() or s.is_neg())
             and torch._C._len_torch_dispatch_stack() == 0
             and torch._C._len_torch_function_stack() == 0
             and torch._C._functorch.peek_interpreter_stack() is None
@@ -86,15 +88,14 @@ class MarlinLinear(torch.nn.Module):
     def forward(self, x: torch.Tensor) -> torch.Tensor:
         if x.shape[-1] != self.in_features:
             raise ValueError("MarlinLinear: last dimension %d, expected %d" % (x.shape[-1], self.in_features))
-        if _plain(x):
-            K, N = self.in_features, self.out_features
+        w, s, K, N = self.w_packed, self.s_packed, self.in_features, self.out_features
+        if _plain(x, w, s):
             if x.dim() == 2:
-                return ops.gemm(x, self.w_packed, self.s_packed, K, N, self.group, sparse=self.sparse)
-            y = ops.gemm(x.reshape(-1, K), self.w_packed, self.s_packed, K, N, self.group, sparse=self.sparse)
+                return ops.gemm(x, w, s, K, N, self.group, sparse=self.sparse)
+            y = ops.gemm(x.reshape(-1, K), w, s, K, N, self.group, sparse=self.sparse)
             return y.view(*x.shape[:-1], N)
-        y = torch.ops.marlin_mi355x.gemm(x.reshape(-1, self.in_features), self.w_packed, self.s_packed,
-                                         self.in_features, self.out_features, self.group, self.sparse)
-        return y.reshape(*x.shape[:-1], self.out_features)
+        y = torch.ops.marlin_mi355x.gemm(x.reshape(-1, K), w, s, K, N, self.group, self.sparse)
+        return y.reshape(*x.shape[:-1], N)
 
     def extra_repr(self) -> str:
         return "in_features=%d, out_features=%d, group=%d, sparse=%s" % (

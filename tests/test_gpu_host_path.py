@@ -88,6 +88,49 @@ def test_the_operator_is_seen(layer):
 
 
 @pytest.mark.gpu
+def test_the_buffers_are_looked_at_too(layer):
+    x = torch.randn(2, 512, device="cuda").half()
+    want = layer(x)
+    # scales that want a gradient: refused in backward, as the operator refuses it
+    layer.s_packed.requires_grad_()
+    y = layer(x)
+    assert y.requires_grad and torch.equal(y, want)
+    with pytest.raises(RuntimeError):
+        y.float().sum().backward()
+    with torch.no_grad():
+        assert not layer(x).requires_grad
+    layer.s_packed.requires_grad_(False)
+
+    # a buffer that is a tensor subclass sees the operator
+    seen = []
+
+    class Watched(torch.Tensor):
+        @classmethod
+        def __torch_function__(cls, func, types, args=(), kwargs=None):
+            seen.append(str(func))
+            return super().__torch_function__(func, types, args, kwargs or {})
+
+    for name in ("w_packed", "s_packed"):
+        seen.clear()
+        plain = getattr(layer, name)
+        setattr(layer, name, plain.as_subclass(Watched))
+        assert torch.equal(layer(x).as_subclass(torch.Tensor), want)
+        assert any("marlin_mi355x" in f for f in seen), name
+        setattr(layer, name, plain)
+
+
+@pytest.mark.gpu
+def test_a_lazily_negated_view_is_read_as_its_values(layer):
+    x = torch.randn(3, 512, device="cuda").half()
+    neg = torch._neg_view(x)  # as the imaginary part of a conjugate is
+    assert neg.is_neg() and torch.equal(layer(neg), layer(-x))
+    layer.s_packed = layer.s_packed.neg()
+    want = layer(x)
+    layer.s_packed = torch._neg_view(layer.s_packed.neg())
+    assert layer.s_packed.is_neg() and torch.equal(layer(x), want)
+
+
+@pytest.mark.gpu
 def test_default_workspace_is_made_once_per_stream(layer):
     x = torch.randn(300, 512, device="cuda").half()
     y = layer(x)
