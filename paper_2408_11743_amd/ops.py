@@ -184,13 +184,14 @@ def quantize(W: torch.Tensor, group=128, ratios=CLIP_RATIOS):
 def quantize_linear(weight: torch.Tensor, group=128, ratios=CLIP_RATIOS):
     """``pack(*quantize(weight.t(), group, ratios), group)`` for a linear
     layer's weight [N, K]: the same bits.  A contiguous weight is read as it
-    lies and packed in the same launch; any other goes through a transposed
-    copy, the codes and ``pack``."""
+    lies and packed in the same launch; any other, a tensor subclass and a
+    lazily negated view go through a transposed copy, the codes and ``pack``."""
     N, K = weight.shape
     g = _group(K, group)
     wb = B.marlin_packed_weight_bytes(K, N)
     sb = B.marlin_packed_scale_bytes(K, N, g)
-    if not (wb and sb and weight.is_cuda and weight.dtype == torch.float16 and weight.is_contiguous()
+    if not (wb and sb and type(weight) in (torch.Tensor, torch.nn.Parameter) and weight.is_cuda
+            and weight.dtype == torch.float16 and weight.is_contiguous() and not weight.is_neg()
             and weight.data_ptr() % 16 == 0):
         q, s = quantize(weight.t().contiguous(), group=group, ratios=ratios)
         return pack(q, s, group=group)

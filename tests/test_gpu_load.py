@@ -55,7 +55,8 @@ def test_any_layout_of_the_weight(mk):
     wide = torch.zeros(N, 2 * K, dtype=torch.float16, device="cuda")
     wide[:, ::2] = w
     transposed = w.t().contiguous().t()
-    for v in (shifted, wide[:, ::2], transposed, torch.nn.Parameter(w)):
+    negated = torch._neg_view(-w)             # as the imaginary part of a conjugate is
+    for v in (shifted, wide[:, ::2], transposed, torch.nn.Parameter(w), negated):
         layer = mk.MarlinLinear.from_float(v)
         assert same((layer.w_packed, layer.s_packed), want)
     with pytest.raises(TypeError):
