@@ -145,7 +145,9 @@ marlin_status_t marlin_unpack_weights(const void *w_packed, const void *s_packed
  * product (stream kernel with row groups of up to 32 rows, tile kernels) or,
  * in the wide kernel that serves large batches and the stream and pair
  * kernels with 64-row groups, the fp16 weights before the product (one fp16 rounding per
- * weight, as Section 3.4's "Groups and Instruction Ordering" does);
+ * weight, as Section 3.4's "Groups and Instruction Ordering" does; which
+ * kernel a call runs, and with it where its scales are rounded, follows from
+ * M, N, K, the device and the workspace size: marlin_describe names it);
  * per-channel scales multiply the final sum once.  Any M up to 4096
  * runs in one launch: the rows are cut into segments (32 or 64 rows for the
  * stream kernel, the tile's rows for the tile and wide kernels) and each segment repeats the

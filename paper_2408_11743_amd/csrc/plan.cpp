@@ -272,6 +272,28 @@ TilePartition best_tile_partition(const Override &ov, int64_t tiles, int KU, int
     return best;
 }
 
+// Which grouped calls the wide kernel may take, that is, which may round their
+// scaled weights to fp16.  A rule about precision, not an estimate: its numbers
+// describe no kernel that is here, and stay as they are when a kernel gets
+// faster, so that no call that kept its scales in fp32 loses them.  Beyond 128
+// rows, a call may round where whole tiles of 128 x 256 at 1.92 us per 128-row
+// block, or of 64 x 512 at 2.15 us, come out ahead of `fp32_us`, the modelled
+// time of the kernels with fp32 scales: most calls of 512 rows and more with N a
+// multiple of 256 (four in five at 512..1023 rows), few below 192.
+bool may_round_scales(const Override &ov, int M, int N, int KU, int64_t grid, size_t partial_budget, double fp32_us)
+{
+    if (M <= 128) return false;
+    const int shapes[2][2] = {{128, 256}, {64, 512}};  // rows, columns
+    for (const auto &sh : shapes) {
+        if (N % sh[1] != 0) continue;
+        const Partition pt = best_partition(ov, (int64_t)(N / sh[1]) * ((M + sh[0] - 1) / sh[0]), KU, grid,
+                                            sh[0] == 128 ? 1.92 : 2.15, 8.0, 2.0, 0.0, (size_t)2 << 17,
+                                            partial_budget);
+        if (pt.t < fp32_us) return true;
+    }
+    return false;
+}
+
 // Stream kernel, dense and 2:4 sparse, up to 64 rows: the time of a launch is
 // a fixed cost, plus per 128-row block of the busiest work-group a unit time
 // (kStreamUnit: by sparsity, rows and tile shape) that grows with the share of
@@ -485,10 +507,8 @@ GemmConfig choose_config(int M, int N, int K, int group_units, int cus, bool spa
     // rounds the scaled weights to fp16 (half of the tile kernel's conversion
     // and scaling per MFMA, 10-15% faster beyond 256 rows), so with group
     // scales it only takes calls that already go to row groups of 64, which do
-    // the same, or beyond 128 rows those for which a kernel with that rounding
-    // is at hand at 1.92 us per 128-row block of a 128 x 256 tile or 2.15 us
-    // of a 64 x 512 one (the four-wave kernels that served them): the others
-    // keep their fp32 scales.
+    // the same, or that may_round_scales lets it have: the others keep their
+    // fp32 scales.
     // Up to 64 rows the row groups of 32 and 64 lead or are within 10%.  The
     // times above are up to 15% too long for whole tiles (the row groups of one
     // column tile share its weights in L2: 8192 x 8192 at M = 128 takes 25.2 us,
@@ -496,17 +516,8 @@ GemmConfig choose_config(int M, int N, int K, int group_units, int cus, bool spa
     // Stream-K ranges over several row groups (23680 x 3200 at M = 280: 102 us,
     // modelled 70.5), hence the two weights on the comparison.
     if (!sparse && (ov.kind < 0 ? M > 64 : ov.kind == kKindWide || ov.kind == kKindTile8)) {
-        bool rounds_weights = group_units == 0 || (cfg.kind == kKindStream && cfg.mb == 4);
-        if (M > 128 && !rounds_weights) {
-            const int shapes[2][2] = {{128, 256}, {64, 512}};
-            for (const auto &sh : shapes) {
-                if (N % sh[1] != 0) continue;
-                const Partition pt = best_partition(ov, (int64_t)(N / sh[1]) * ((M + sh[0] - 1) / sh[0]), KU, grid,
-                                                    sh[0] == 128 ? 1.92 : 2.15, 8.0, 2.0, 0.0, (size_t)2 << 17,
-                                                    partial_budget);
-                rounds_weights = rounds_weights || pt.t < best;
-            }
-        }
+        const bool rounds_weights = group_units == 0 || (cfg.kind == kKindStream && cfg.mb == 4) ||
+                                    may_round_scales(ov, M, N, KU, grid, partial_budget, best);
         if (ov.kind < 0) best *= cfg.whole ? 0.93 : 1.08;
         for (int shape = 0; shape < 3; ++shape) {  // wide 128 x 256, tile 128 x 256, tile 64 x 256
             const int kind = shape == 0 ? kKindWide : kKindTile8;
