@@ -8,6 +8,14 @@
 #include "internal.h"
 
 namespace marlin {
+
+// Last template argument of the eight-wave tile and wide kernels; it sets
+// their names apart from those of tile.hip's.
+template <bool PER_CHANNEL>
+struct EightWaves {
+    static constexpr bool per_channel = PER_CHANNEL;
+};
+
 namespace dev {
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
@@ -145,6 +153,20 @@ __device__ __forceinline__ half8_t dequant_magic(uint32_t x, const DequantConsts
     const half2_t r2 = as_h2((y & k.lo) | k.ex) - sub;
     const half2_t r3 = __builtin_elementwise_fma(as_h2((y & k.hi) | k.ex), mul, add);
     return half8_t{r0.x, r0.y, r1.x, r1.y, r2.x, r2.y, r3.x, r3.y};
+}
+
+// A quarter of the same, codes 2q and 2q + 1, times the scale (SCALED, one
+// rounding): the eight-wave kernels place one after each MFMA or every other.
+template <bool SCALED>
+__device__ __forceinline__ half2_t magic_quarter(uint32_t x, int q, half2_t s2, const DequantConsts &k)
+{
+    const half2_t sub = {(_Float16)1032.0f, (_Float16)1032.0f};
+    const half2_t mul = {(_Float16)0.0625f, (_Float16)0.0625f};
+    const half2_t add = {(_Float16)-72.0f, (_Float16)-72.0f};
+    const uint32_t y = (q >> 1) ? x >> 8 : x;
+    const half2_t r = (q & 1) == 0 ? as_h2((y & k.lo) | k.ex) - sub
+                                   : __builtin_elementwise_fma(as_h2((y & k.hi) | k.ex), mul, add);
+    return SCALED ? r * s2 : r;
 }
 
 // Scale row of 128-row block ku: ku / group_units as one multiply-high with

@@ -30,10 +30,10 @@
 #include "device.h"
 #include "internal.h"
 
-namespace {  // outside marlin: the kernel's name is what marlin_describe prints
+namespace marlin {
+namespace {
 
-using namespace marlin;
-using namespace marlin::dev;
+using namespace dev;
 
 constexpr int kPairP = 3;                      // ring slots
 constexpr int kPairA = 64 * 256;               // a block's 64 rows x 128 k, bytes
@@ -41,20 +41,6 @@ constexpr int kPairWAt = 2 * kPairA;           // then the waves' words (2 KiB e
 constexpr int kPairSAt = kPairWAt + 8 * 2048;  // and scale rows (256 B each)
 constexpr int kPairStage = kPairSAt + 8 * 256;
 static_assert(kPairP * kPairStage <= 160 * 1024 - 64, "LDS");
-
-// One quarter (codes 2q and 2q + 1) of a word: q - 8 exactly by the magic
-// number, times the scale (SCALED, one rounding).
-template <bool SCALED>
-__device__ __forceinline__ half2_t pair_quarter(uint32_t x, int q, half2_t s2, const DequantConsts &k)
-{
-    const half2_t sub = {(_Float16)1032.0f, (_Float16)1032.0f};
-    const half2_t mul = {(_Float16)0.0625f, (_Float16)0.0625f};
-    const half2_t add = {(_Float16)-72.0f, (_Float16)-72.0f};
-    const uint32_t y = (q >> 1) ? x >> 8 : x;
-    const half2_t r = (q & 1) == 0 ? as_h2((y & k.lo) | k.ex) - sub
-                                   : __builtin_elementwise_fma(as_h2((y & k.hi) | k.ex), mul, add);
-    return SCALED ? r * s2 : r;
-}
 
 template <bool PER_CHANNEL>
 __global__ void __launch_bounds__(512, 1) w4a16_pair_kernel(GemmProblem p)
@@ -229,7 +215,7 @@ __global__ void __launch_bounds__(512, 1) w4a16_pair_kernel(GemmProblem p)
     // the next operand's conversion
     auto slot = [&](int t, int b, int mb, half8_t w, uint32_t next, half2_t ns) {
         acc[b][mb] = mfma(w, __builtin_bit_cast(half8_t, av[t][mb]), acc[b][mb]);
-        nx[mb] = pair_quarter<!PER_CHANNEL>(next, mb, ns, dq);
+        nx[mb] = magic_quarter<!PER_CHANNEL>(next, mb, ns, dq);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto operand = [&]() {
@@ -334,7 +320,7 @@ __global__ void __launch_bounds__(512, 1) w4a16_pair_kernel(GemmProblem p)
 #pragma unroll
     for (int b = 0; b < NB; ++b) wv[b] = wn_[b];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) nx[q] = pair_quarter<!PER_CHANNEL>(wv[0][0], q, s2[0], dq);
+    for (int q = 0; q < 4; ++q) nx[q] = magic_quarter<!PER_CHANNEL>(wv[0][0], q, s2[0], dq);
     // k-steps 0 and 1 of stage 0
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -443,8 +429,6 @@ __global__ void __launch_bounds__(512, 1) w4a16_pair_kernel(GemmProblem p)
 }
 
 }  // namespace
-
-namespace marlin {
 
 hipError_t launch_pair_gemm(const GemmConfig &cfg, const GemmProblem &p, hipStream_t stream)
 {

@@ -62,22 +62,6 @@ struct Tile8Shape {
     static_assert(P >= 3, "ring too shallow");
 };
 
-template <bool PER_CHANNEL>
-struct EightWaves {
-    static constexpr bool per_channel = PER_CHANNEL;
-};
-
-// One quarter (codes 2q and 2q + 1) of a word by the magic number: exact q - 8.
-__device__ __forceinline__ half2_t magic_quarter(uint32_t x, int q, const DequantConsts &k)
-{
-    const half2_t sub = {(_Float16)1032.0f, (_Float16)1032.0f};
-    const half2_t mul = {(_Float16)0.0625f, (_Float16)0.0625f};
-    const half2_t add = {(_Float16)-72.0f, (_Float16)-72.0f};
-    const uint32_t y = (q >> 1) ? x >> 8 : x;
-    return (q & 1) == 0 ? as_h2((y & k.lo) | k.ex) - sub
-                        : __builtin_elementwise_fma(as_h2((y & k.hi) | k.ex), mul, add);
-}
-
 template <int WN, int WM, int MBW, int NBW, int KS, typename SCALES>
 __global__ void __launch_bounds__(64 * WN * WM, 1) w4a16_tile_kernel(GemmProblem p)
 {
@@ -266,7 +250,7 @@ __global__ void __launch_bounds__(64 * WN * WM, 1) w4a16_tile_kernel(GemmProblem
     auto slot = [&](int b, int k, half8_t w, uint32_t next, int fb, bool prev) {
         const int t = k / MBW, mb = k % MBW;
         tmp[b & 1][mb] = mfma(w, __builtin_bit_cast(half8_t, av[t][mb]), t == 0 ? zero4 : tmp[b & 1][mb]);
-        nx[mb] = magic_quarter(next, mb, dq);
+        nx[mb] = magic_quarter<false>(next, mb, half2_t{}, dq);
         if (fb >= 0) fold(fb, mb, t, prev);
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -360,7 +344,7 @@ __global__ void __launch_bounds__(64 * WN * WM, 1) w4a16_tile_kernel(GemmProblem
 #pragma unroll
     for (int i = 0; i < kSRd; ++i) asm volatile("" : "+v"(sv[i]));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) nx[q] = magic_quarter(wv[0][0], q, dq);
+    for (int q = 0; q < 4; ++q) nx[q] = magic_quarter<false>(wv[0][0], q, half2_t{}, dq);
     // column blocks 0 .. NBW - 2 of a stage
     auto mid_blocks = [&](int b_from) {
 #pragma unroll

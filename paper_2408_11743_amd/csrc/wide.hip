@@ -55,25 +55,6 @@ struct WideShape {
     static_assert(P * kStage <= 160 * 1024 - 64, "LDS");
 };
 
-// One quarter (codes 2q and 2q + 1) of a word: q - 8 exactly by the magic
-// number, times the scale (SCALED, one rounding).
-template <bool SCALED>
-__device__ __forceinline__ half2_t wide_quarter(uint32_t x, int q, half2_t s2, const DequantConsts &k)
-{
-    const half2_t sub = {(_Float16)1032.0f, (_Float16)1032.0f};
-    const half2_t mul = {(_Float16)0.0625f, (_Float16)0.0625f};
-    const half2_t add = {(_Float16)-72.0f, (_Float16)-72.0f};
-    const uint32_t y = (q >> 1) ? x >> 8 : x;
-    const half2_t r = (q & 1) == 0 ? as_h2((y & k.lo) | k.ex) - sub
-                                   : __builtin_elementwise_fma(as_h2((y & k.hi) | k.ex), mul, add);
-    return SCALED ? r * s2 : r;
-}
-
-template <bool PER_CHANNEL>
-struct EightWaves {
-    static constexpr bool per_channel = PER_CHANNEL;
-};
-
 template <int MB, int NB, int P, typename SCALES>
 __global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
 {
@@ -264,7 +245,7 @@ __global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
     // also converts a quarter of the next operand's word
     auto slot = [&](int t, int b, int mb, half8_t w, uint32_t next, half2_t ns) {
         acc[b][mb] = mfma(w, __builtin_bit_cast(half8_t, av[t][mb]), acc[b][mb]);
-        if ((mb & 1) == 0) nx[mb >> 1] = wide_quarter<!PER_CHANNEL>(next, mb >> 1, ns, dq);
+        if ((mb & 1) == 0) nx[mb >> 1] = magic_quarter<!PER_CHANNEL>(next, mb >> 1, ns, dq);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto operand = [&]() {
@@ -375,7 +356,7 @@ __global__ void __launch_bounds__(512, 1) w4a16_wide_kernel(GemmProblem p)
     landed_ws(NB);
     scales();
 #pragma unroll
-    for (int q = 0; q < 4; ++q) nx[q] = wide_quarter<!PER_CHANNEL>(wv[0][0], q, s2[0], dq);
+    for (int q = 0; q < 4; ++q) nx[q] = magic_quarter<!PER_CHANNEL>(wv[0][0], q, s2[0], dq);
     // first k-step of stage 0
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
