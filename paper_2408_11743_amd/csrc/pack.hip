@@ -28,8 +28,8 @@ __device__ __forceinline__ int nibble_of(int j) { return (j >> 1) + 4 * (j & 1);
 // bytes of a row and a wave four octets of rows, and the thread's words are four
 // 16-byte vectors (t = 0..3) of adjacent lanes of the packed layout.  Rows j and
 // j + 2 share a byte (v_lshl_or), then a 4 x 4 byte transpose gives the columns'
-// words.  Bound by memory: 8192 x 28672 in 85 us, either way (one thread per
-// word, eight byte accesses each: 176 us packing, 239 unpacking).
+// words.  Bound by memory: 8192 x 28672 in 89 us packing, 90 unpacking (one
+// thread per word, eight byte accesses each: 177 and 260).
 // (q may have any alignment: callers pass views of larger buffers)
 __device__ __forceinline__ uint32_t load_codes(const uint8_t *p)
 {

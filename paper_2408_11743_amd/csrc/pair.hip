@@ -21,9 +21,11 @@
 // branch: the compiler takes their registers as written and could move them.
 //
 // Bound: LDS bandwidth and vector issue (193 KiB of LDS traffic and 3.25 vector
-// instructions per MFMA in a stage).  8192 x 28672 at M = 64 44.5 us (before
-// 46.5); without the conversion 36.0, without the loads 36.6, without both 26.1;
-// 4096 x 11008 at M = 128 21.2 us (24.2), 1792 x 14592 at M = 114 13.2 (15.3).
+// instructions per MFMA in a stage).  In one process with the kernel before it
+// (a burst of loads and two barriers per stage): 8192 x 28672 at M = 64 44.2 us
+// (45.7), per channel 39.4 (42.1), M = 33 39.4 (41.1); 4096 x 11008 at M = 128
+// 21.3 (24.2), 1792 x 14592 at M = 114 12.9 (15.1).  Timing-only copies at
+// M = 64: without the conversion 36.0, without the loads 36.6, without both 26.1.
 #include <hip/hip_runtime.h>
 #include <stdio.h>
 

@@ -28,7 +28,7 @@
 // because t s (4 by 11 bits) is exact.  28672 x 8192 with ten ratios: 332 us at
 // g = 128 (seven operations per term: 393; 21 clocks per term and SIMD, of which
 // the rounding and the clamp, at half rate, take 9); 4096 x 11008 per channel
-// 220 us (a thread per group re-reading it for each ratio: 3650).  Loading a
+// 230 us (a thread per group re-reading it for each ratio: 3650).  Loading a
 // 4096 x 11008 linear layer: 83 us (transposed copy, quantiser and packer: 427).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
