@@ -29,7 +29,8 @@ Sections beside the step, outside its timed region: ``attention_4096`` (the
 Llama-7B attention projection, 4096 x 4096), ``mlp_7b`` (the Llama-7B MLP
 layers, g = 128 and per-channel scales), ``sparse_2of4`` (the 2:4 sparse
 kernel, 8192 x 8192), ``prefill`` (M = 256, 1024, 4096 in one launch per
-call) and ``quantize`` (the weight quantiser).
+call) and ``quantize`` (the weight quantiser).  The headline's line holds
+their main figures, layer by layer; ``--only SECTION`` prints all of them.
 
 Usage: python bench.py [--gpus 1] [--steps K] [--warmup W] [--no-cpu-baseline]
        [--no-sections] [--no-clock] [--only SECTION] [--profile-cases C
@@ -615,6 +616,28 @@ def run_section(name, args, mk, R, synth, torch, np, dev):
     return quantize_section(args, mk, R, synth, torch, np, dev)
 
 
+def brief(section):
+    """A section as it stands in the headline's line: its rows column by column
+    (one entry per layer, lists over M) with the figures a reader compares, and
+    no per-case oracle times, so that the line stays short enough to be kept
+    whole.  `--only SECTION` prints every figure."""
+    keep = ("us", "TFLOPs", "roof_frac", "mfma_frac", "speedup_vs_fp16", "speedup_vs_dense_w4")
+    out = dict(section)
+    layers = {}
+    for r in section.get("per_m", ()):
+        key = tuple((k, r[k]) for k in ("K", "N", "group") if k in r)
+        lay = layers.setdefault(key, {**dict(key), "M": []})
+        lay["M"].append(r["M"])
+        for k in keep:
+            if k in r:
+                lay.setdefault(k, []).append(r[k])
+    if layers:
+        out["per_m"] = list(layers.values())
+    if out.get("cpu_baseline"):
+        out["cpu_baseline"] = {k: v for k, v in out["cpu_baseline"].items() if k != "per_case"}
+    return out
+
+
 def single_thread_oracle():
     """The oracle on one thread (the 8192 x 28672 layer at M = 1), in a child
     process started with OMP_NUM_THREADS=1."""
@@ -898,7 +921,7 @@ def main():
         "cpu_baseline": cpu,
         "parity": parity,
     }
-    out.update(sections)
+    out.update({name: brief(s) for name, s in sections.items()})
     print(json.dumps(out), flush=True)
 
 
