@@ -214,8 +214,9 @@ marlin_status_t marlin_gemm_no_alloc(const uint16_t *A, const void *w_packed, co
  * problem on the current device (or on a 256-CU device when no device is
  * visible), as one NUL-terminated line: the kernel's name with its template
  * arguments as a profiler reports it, then "cols=<columns per tile>
- * rg=<row groups> partition=<whole|streamk|hybrid> grid=<work-groups>", for the
- * first launch (the first 4096 rows).  The stream kernel's template arguments are
+ * rg=<row groups> partition=<whole|streamk> grid=<work-groups>" (and, where
+ * whole tiles follow the shared ones, "hybrid=<shared tiles>" before the
+ * partition), for the first launch (the first 4096 rows).  The stream kernel's template arguments are
  * <16-row blocks, 16-column blocks, ring depth, activation rows / 4, waves,
  * per-channel>, the tile kernel's <waves along N, waves along M, 16-row
  * blocks per wave, 16-column blocks per wave, 128-row blocks per stage,

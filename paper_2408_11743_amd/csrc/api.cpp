@@ -159,10 +159,15 @@ marlin_status_t describe_impl(int64_t M, int64_t N, int64_t K, int64_t group, ch
     const GemmConfig cfg = plan_pass(mp, (int)N, (int)K, gu, cus, sparse, SIZE_MAX, current_override());
     char name[96];
     kernel_name(cfg, gu == 0, name, sizeof(name));
+    char hybrid[24] = "";
+    if (cfg.hybrid) {
+        const Ranges r = ranges_of(cfg, (int)N, (int)K);
+        snprintf(hybrid, sizeof(hybrid), "hybrid=%d ", r.units / (int)(K / 128));
+    }
     if (buf_bytes > 0)
-        snprintf(buf, buf_bytes, "%s cols=%d rg=%d partition=%s grid=%d", name,
-                 tile_cols(cfg), cfg.rg,
-                 cfg.hybrid ? "hybrid" : cfg.whole ? "whole" : "streamk", cfg.grid);
+        snprintf(buf, buf_bytes, "%s cols=%d rg=%d %spartition=%s grid=%d", name,
+                 tile_cols(cfg), cfg.rg, hybrid,
+                 cfg.whole ? "whole" : "streamk", cfg.grid);
     return MARLIN_OK;
 }
 }  // namespace
