@@ -24,7 +24,7 @@
 //  * Partition: device.h's ranges over shared tiles, then whole tiles (the
 //    hybrid, plan.cpp); shared tiles are combined wave by wave.
 //
-// Bound: vector issue and power.  At 28672 x 8192, M = 1024 (one box): 415 us,
+// Bound: vector issue and power.  At 28672 x 8192, M = 1024 (one run): 415 us,
 // without the fold 378, without the conversion 396, without the loads 373,
 // without the LDS reads 411, MFMAs alone 293; the shader clock drops to 1.95
 // GHz.  Against the kernels it takes over from: 8192 x 28672 at M = 128 71.4 us
