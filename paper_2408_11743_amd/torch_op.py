@@ -44,23 +44,32 @@ def _gemm_fake(A, w_packed, s_packed, K, N, group, sparse=False):
     return A.new_empty((A.shape[0], N))
 
 
+# What the check below asks of torch, bound once: looking the names up took as
+# long as asking.
+_Tensor, _grad_enabled = torch.Tensor, torch.is_grad_enabled
+_dispatch_modes, _function_modes = torch._C._len_torch_dispatch_stack, torch._C._len_torch_function_stack
+_transforms, _tracing = torch._C._functorch.peek_interpreter_stack, torch._C._get_tracing_state
+_forward_ad, _profiling = torch.autograd.forward_ad, torch.autograd._profiler_enabled
+
+
 def _plain(x: torch.Tensor, w: torch.Tensor, s: torch.Tensor) -> bool:
     """Nothing but the CUDA implementation would see the operator's call on
     these three tensors: no tracing or compiling, no subclass, mode, transform,
     dual level or profiler, no gradient, no lazily negated view.  The layer then
     calls it directly: the operator's dispatch (5 us through Python, 28 -> 12 us
-    a call with the above) is as long as a small decode GEMM."""
+    a call with the above) is as long as a small decode GEMM.  (Where the
+    buffers are is checked by the call itself; packed bytes have no sign.)"""
     return (not torch.compiler.is_compiling()
-            and type(x) is torch.Tensor and type(w) is torch.Tensor and type(s) is torch.Tensor
-            and x.is_cuda and w.is_cuda and s.is_cuda
-            and not ((x.requires_grad or s.requires_grad) and torch.is_grad_enabled())
-            and not (x.is_neg() or w.is_neg() or s.is_neg())
-            and torch._C._len_torch_dispatch_stack() == 0
-            and torch._C._len_torch_function_stack() == 0
-            and torch._C._functorch.peek_interpreter_stack() is None
-            and torch._C._get_tracing_state() is None
-            and torch.autograd.forward_ad._current_level < 0
-            and not torch.autograd._profiler_enabled())
+            and type(x) is _Tensor and type(w) is _Tensor and type(s) is _Tensor
+            and x.is_cuda
+            and not ((x.requires_grad or s.requires_grad) and _grad_enabled())
+            and not x.is_neg() and not s.is_neg()
+            and _dispatch_modes() == 0
+            and _function_modes() == 0
+            and _transforms() is None
+            and _tracing() is None
+            and _forward_ad._current_level < 0
+            and not _profiling())
 
 
 class MarlinLinear(torch.nn.Module):
